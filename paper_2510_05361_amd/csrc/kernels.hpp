@@ -28,9 +28,15 @@ constexpr int kMaxMeanStates = 2 + kMaxN;
 enum Form { kAdam = 0, kAdopt = 1, kSgdm = 2 };
 enum AdoptOrder { kPrev = 0, kCur = 1 };
 
-typedef float f32x4 __attribute__((ext_vector_type(4)));
-typedef uint16_t u16x4 __attribute__((ext_vector_type(4)));
-typedef uint16_t u16x8 __attribute__((ext_vector_type(8)));
+// scalars, and vectors at addresses aligned to their element only
+struct f32x1 { using type = float; };
+struct f32x4 { typedef float type __attribute__((ext_vector_type(4), aligned(4))); };
+struct u16x1 { using type = uint16_t; };
+struct u16x4 { typedef uint16_t type __attribute__((ext_vector_type(4), aligned(2))); };
+struct u16x8 { typedef uint16_t type __attribute__((ext_vector_type(8), aligned(2))); };
+
+template <bool B>
+struct BoolC { static constexpr bool value = B; };
 
 // ------------------------------------------------------------ conversions
 
@@ -53,22 +59,43 @@ __device__ __forceinline__ T load_uniform(const T* p) {
   return *(const __attribute__((address_space(4))) T*)p;
 }
 
+// Uniform device pointers, in scalar registers from here on, all in one
+// round of scalar loads (the address space goes with them: behind asm a
+// plain pointer would be a flat one).
+template <typename A, typename B, typename C, typename D>
+__device__ __forceinline__ void in_sgprs(A*& a, B*& b, C*& c, D*& d) {
+  typedef A __attribute__((address_space(1)))* GA;
+  typedef B __attribute__((address_space(1)))* GB;
+  typedef C __attribute__((address_space(1)))* GC;
+  typedef D __attribute__((address_space(1)))* GD;
+  GA qa = (GA)a;
+  GB qb = (GB)b;
+  GC qc = (GC)c;
+  GD qd = (GD)d;
+  asm volatile("" : "+s"(qa), "+s"(qb), "+s"(qc), "+s"(qd));
+  a = (A*)qa;
+  b = (B*)qb;
+  c = (C*)qc;
+  d = (D*)qd;
+}
+
 // --------------------------------------------------- vector load / store
 //
 // load_v<T, V>(p, e, out): V consecutive elements starting at element e,
 // widened to fp32.  T = float, or uint16_t holding bf16 bit patterns.  V = 1 (scalar path for rows whose
 // length breaks 16-byte alignment), 4 or 8.
 
+// (vector types go by alias: a deduced type would lose the alignment)
 template <bool NT, typename VT>
-__device__ __forceinline__ VT ld(const VT* p) {
-  if constexpr (NT) return __builtin_nontemporal_load(p);
-  else return *p;
+__device__ __forceinline__ typename VT::type ld(const void* p) {
+  if constexpr (NT) return __builtin_nontemporal_load(reinterpret_cast<const typename VT::type*>(p));
+  else return *reinterpret_cast<const typename VT::type*>(p);
 }
 
 template <bool NT, typename VT>
-__device__ __forceinline__ void st(VT* p, VT v) {
-  if constexpr (NT) __builtin_nontemporal_store(v, p);
-  else *p = v;
+__device__ __forceinline__ void st(void* p, typename VT::type v) {
+  if constexpr (NT) __builtin_nontemporal_store(v, reinterpret_cast<typename VT::type*>(p));
+  else *reinterpret_cast<typename VT::type*>(p) = v;
 }
 
 template <typename T, int V, bool NT>
@@ -76,26 +103,26 @@ __device__ __forceinline__ void load_v(const T* __restrict__ p, int64_t e, float
   if constexpr (sizeof(T) == 4) {
     const float* q = reinterpret_cast<const float*>(p) + e;
     if constexpr (V == 1) {
-      o[0] = ld<NT>(q);
+      o[0] = ld<NT, f32x1>(q);
     } else {
 #pragma unroll
       for (int k = 0; k < V / 4; ++k) {
-        f32x4 a = ld<NT>(reinterpret_cast<const f32x4*>(q) + k);
+        const f32x4::type a = ld<NT, f32x4>(q + 4 * k);
         o[4 * k + 0] = a.x; o[4 * k + 1] = a.y; o[4 * k + 2] = a.z; o[4 * k + 3] = a.w;
       }
     }
   } else {
     const uint16_t* q = reinterpret_cast<const uint16_t*>(p) + e;
     if constexpr (V == 1) {
-      o[0] = bf16_to_f32(ld<NT>(q));
+      o[0] = bf16_to_f32(ld<NT, u16x1>(q));
     } else if constexpr (V == 4) {
-      u16x4 a = ld<NT>(reinterpret_cast<const u16x4*>(q));
+      const u16x4::type a = ld<NT, u16x4>(q);
 #pragma unroll
       for (int k = 0; k < 4; ++k) o[k] = bf16_to_f32(a[k]);
     } else {
 #pragma unroll
       for (int k = 0; k < V / 8; ++k) {
-        u16x8 a = ld<NT>(reinterpret_cast<const u16x8*>(q) + k);
+        const u16x8::type a = ld<NT, u16x8>(q + 8 * k);
 #pragma unroll
         for (int t = 0; t < 8; ++t) o[8 * k + t] = bf16_to_f32(a[t]);
       }
@@ -108,33 +135,89 @@ __device__ __forceinline__ void store_v(T* __restrict__ p, int64_t e, const floa
   if constexpr (sizeof(T) == 4) {
     float* q = reinterpret_cast<float*>(p) + e;
     if constexpr (V == 1) {
-      st<NT>(q, o[0]);
+      st<NT, f32x1>(q, o[0]);
     } else {
 #pragma unroll
       for (int k = 0; k < V / 4; ++k) {
-        f32x4 a = {o[4 * k + 0], o[4 * k + 1], o[4 * k + 2], o[4 * k + 3]};
-        st<NT>(reinterpret_cast<f32x4*>(q) + k, a);
+        const f32x4::type a = {o[4 * k + 0], o[4 * k + 1], o[4 * k + 2], o[4 * k + 3]};
+        st<NT, f32x4>(q + 4 * k, a);
       }
     }
   } else {
     uint16_t* q = reinterpret_cast<uint16_t*>(p) + e;
     if constexpr (V == 1) {
-      st<NT>(q, f32_to_bf16(o[0]));
+      st<NT, u16x1>(q, f32_to_bf16(o[0]));
     } else if constexpr (V == 4) {
-      u16x4 a;
+      u16x4::type a;
 #pragma unroll
       for (int k = 0; k < 4; ++k) a[k] = f32_to_bf16(o[k]);
-      st<NT>(reinterpret_cast<u16x4*>(q), a);
+      st<NT, u16x4>(q, a);
     } else {
 #pragma unroll
       for (int k = 0; k < V / 8; ++k) {
-        u16x8 a;
+        u16x8::type a;
 #pragma unroll
         for (int t = 0; t < 8; ++t) a[t] = f32_to_bf16(o[8 * k + t]);
-        st<NT>(reinterpret_cast<u16x8*>(q) + k, a);
+        st<NT, u16x8>(q + 8 * k, a);
       }
     }
   }
+}
+
+// Accesses of up to V elements at base + o: all V as one vector access
+// (FULL), or the first n < V element by element, zeros for the others.
+// base is the same in every lane and o a 32-bit element offset, so an access
+// takes a scalar base and one vector register: with a 64-bit element index
+// per lane each stream held two registers of address from its load to its
+// store.  Rows start at any element (row m at m P), so base + o is aligned
+// to its element only; the hardware takes 16-byte accesses at any 4-byte
+// (fp32) or 2-byte (bf16) address.
+template <typename T>
+__device__ __forceinline__ const T* at(const T* base, uint32_t o) {
+  return reinterpret_cast<const T*>(reinterpret_cast<const char*>(base) + (uint32_t)(o * (uint32_t)sizeof(T)));
+}
+
+template <typename T>
+__device__ __forceinline__ T* at(T* base, uint32_t o) {
+  return reinterpret_cast<T*>(reinterpret_cast<char*>(base) + (uint32_t)(o * (uint32_t)sizeof(T)));
+}
+
+template <bool FULL, typename T, int V, bool NT>
+__device__ __forceinline__ void load_n(const T* base, uint32_t o, int32_t n, float (&a)[V]) {
+  if constexpr (FULL) {
+    load_v<T, V, NT>(at(base, o), 0, a);
+  } else {
+    // a copy of o that the compiler cannot see through: an address that both
+    // paths share would be formed before them in vector registers
+    asm("" : "+v"(o));
+#pragma unroll
+    for (int t = 0; t < V; ++t) {
+      float b[1] = {0.0f};
+      if (t < n) load_v<T, 1, false>(at(base, o), t, b);
+      a[t] = b[0];
+    }
+  }
+}
+
+template <bool FULL, typename T, int V, bool NT>
+__device__ __forceinline__ void store_n(T* base, uint32_t o, int32_t n, const float (&a)[V]) {
+  if constexpr (FULL) {
+    store_v<T, V, NT>(at(base, o), 0, a);
+  } else {
+    asm("" : "+v"(o));  // as in load_n
+#pragma unroll
+    for (int t = 0; t < V; ++t) {
+      const float b[1] = {a[t]};
+      if (t < n) store_v<T, 1, false>(at(base, o), t, b);
+    }
+  }
+}
+
+// Elements from `from` to the end of a row, as a 32-bit count (callers
+// subtract lane offsets far below 2^30 from it).
+__device__ __forceinline__ int32_t left_in_row(int64_t from, int64_t end) {
+  const int64_t n = end - from;
+  return n > (1 << 30) ? (1 << 30) : n < 0 ? 0 : (int32_t)n;
 }
 
 // ------------------------------------------------------ tile -> elements
@@ -174,6 +257,57 @@ __host__ __device__ constexpr int64_t tiles_for(int64_t P) {
     const int64_t per8 = 8 * (int64_t)(T / C);  // pieces covered by 8 consecutive tiles
     return (pieces + per8 - 1) / per8 * 8;
   }
+}
+
+// The tile of this workgroup: tiles are numbered along x, then y, in
+// dispatch order (a launch's x extent is limited to 2^32 threads).  One tile
+// per workgroup and no loop over tiles: a loop makes the compiler keep every
+// stream's base + lane offset in vector registers across it, in place of a
+// scalar base and one offset.
+__device__ __forceinline__ int64_t launch_tile() { return (int64_t)blockIdx.y * gridDim.x + blockIdx.x; }
+
+// ------------------------------------------------------ launch shapes
+
+// Grid of kernels that take launch_tile(): tiles along x, then y, with the
+// thread count of x below 2^32 for workgroups of up to 1024.  x is a
+// multiple of 16, so a tile's XCD (dispatch order mod 8) and its parity are
+// those of its number.
+inline dim3 tile_grid(int64_t tiles, int32_t nz = 1) {
+  const int64_t maxx = INT64_C(1) << 21;
+  if (tiles < 1) tiles = 1;
+  const int64_t y = (tiles + maxx - 1) / maxx;
+  return dim3((unsigned)(y == 1 ? tiles : maxx), (unsigned)y, (unsigned)nz);
+}
+
+// Workgroups per CU of the streaming kernels.  Bytes in flight beyond what
+// covers the HBM's latency only spread the accesses over more DRAM pages:
+// about 40 KiB of loads per CU ran fastest for every mix of streams, against
+// up to 192 KiB at full occupancy.  A launch limits the workgroups that a CU
+// holds at once by asking for LDS it does not use: 160 KiB per CU, in units
+// of 1280 bytes; a workgroup may ask for 51 units, which leaves two.
+// Passes that load less than kResidentMin bytes hit the 256 MB MALL more than the
+// HBM and keep every wave that the CUs hold (Adam N = 3, 4 replicas, limited
+// against not: 88 MB 15.5 us against 15.1 us, 176 MB 29.3 us against
+// 30.3 us, 352 MB 57.2 us against 59.2 us).
+constexpr int64_t kResidentMin = INT64_C(64) << 20;
+constexpr size_t resident_lds(int n) { return (size_t)(128 / n > 51 ? 51 : 128 / n) * 1280; }
+
+// The local step's workgroups for `bytes` loaded per element (four elements
+// per lane): two waves each, for steps of the limit that are fine enough,
+// and from six 4-byte streams on two workgroups of four waves (354M x 4
+// Adam N = 3: 9.95 ms, against 10.29 ms with four of two waves).  At full
+// occupancy -> limited, on the same buffers of an MI355X: 16.8M x 4 Adam
+// N = 3 497 -> 457 us, 354M x 4 11.02 -> 10.09 ms; 124M x 8 ADOPT N = 2 in
+// bf16 4.97 -> 4.58 ms; 124M x 16 SGDM N = 2 9.28 -> 8.59 ms; 60M x 2 Adam
+// N = 1 564 -> 505 us.
+struct StepLaunch {
+  int threads;   // of a workgroup
+  int resident;  // workgroups per CU
+  int bytes;     // loaded per element
+};
+constexpr StepLaunch step_launch(int bytes) {
+  if (bytes > 20) return {256, 2, bytes};
+  return {128, (40 * 1024 / 2 + 128 * bytes) / (256 * bytes), bytes};
 }
 
 // ------------------------------------------------------------ OuterOpt
@@ -228,8 +362,6 @@ __device__ __forceinline__ void outer_step_piece(const OuterParams& o, int64_t e
 }
 
 // ------------------------------------------------------------ local step
-
-enum StepWindows { kWinOne = 0, kWinHalves = 1, kWinPairs = 2 };
 
 // The update count kept on the device for graph replay (the layout of
 // mtdao_device_step): a launch at offset k after the last advance takes
@@ -287,8 +419,9 @@ struct StepParams {
   float* v;                // [K][P] second moment (Adam, ADOPT)
   const float* scale;      // [K] global-norm clip factors, or nullptr
   int64_t P;               // row length
-  int64_t tiles;           // tiles of one row (all windows)
-  int64_t wlen;            // k_local_step, kWinHalves: elements of the first window
+  int64_t tiles;           // tiles of the launch
+  int64_t n;               // k_local_step: K P, elements of a state
+  double rp;               // 1 / P
   int32_t replicas;        // K
   float beta[kMaxN];       // beta_{1,j}
   float omb[kMaxN];        // 1 - beta_{1,j}
@@ -312,17 +445,19 @@ struct StepParams {
   BiasCorrection bc;
 };
 
-// A value every lane of the wave holds, moved to a scalar register (the
-// fp64 arithmetic below runs in the vector ALU, whose results would
-// otherwise each hold a vector register for the rest of the kernel).
-__device__ __forceinline__ float wave_uniform(float v) {
-  return __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, v)));
+// The value that lane l (the same for the whole wave) holds, in a scalar
+// register: the fp64 arithmetic below runs in the vector ALU, whose results
+// would otherwise each hold a vector register for the rest of the kernel.
+__device__ __forceinline__ float lane_value(float v, int l) {
+  return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), l));
 }
 
 // The launch's scalars: those of the argument block, or those of the
-// device-side update number when it is given (every workgroup forms them;
-// a few dozen double multiplies).  Called where every lane of the wave is
-// active.
+// device-side update number when it is given (every wave forms them).  Lane
+// j forms the weight of moment j (lane n: 1 / (1 - beta_2^s)) with
+// step_scalars' operations, and the results are read across: one power and
+// one quotient per wave in place of n + 1 in turn.  Called where every lane
+// of the wave is active.
 __device__ __forceinline__ StepParams device_scalars(const StepParams& p0) {
 #pragma clang fp contract(off)
   if (p0.dev == nullptr) return p0;
@@ -331,14 +466,21 @@ __device__ __forceinline__ StepParams device_scalars(const StepParams& p0) {
   const int64_t i = (s < p0.table_len ? s : p0.table_len) - 1;
   p.lr = load_uniform(p0.lr_table + i);
   p.clip = p0.clip_table != nullptr ? load_uniform(p0.clip_table + i) : 0.0f;
-  // step_scalars with the moment loop unrolled (a runtime-indexed store
-  // would put the whole parameter block in private memory)
+  const int lane = threadIdx.x & 63;
+  float beta = p0.bc.beta2, omega = 1.0f;
+#pragma unroll
+  for (int j = 0; j < kMaxN; ++j) {
+    float b = p0.bc.beta[j], o = p0.bc.omega[j];
+    asm("" : "+s"(b), "+s"(o));  // selects of values: not a load from a selected address
+    const bool mine = j < p0.bc.n && lane == j;
+    beta = mine ? b : beta;
+    omega = mine ? o : omega;
+  }
+  const float w = (float)(p0.bc.on ? (double)omega / (1.0 - pow_steps((double)beta, s)) : (double)omega);
 #pragma unroll
   for (int j = 0; j < kMaxN; ++j)
-    if (j < p0.bc.n)
-      p.w[j] = wave_uniform((float)(p0.bc.on ? (double)p0.bc.omega[j] / (1.0 - pow_steps((double)p0.bc.beta[j], s))
-                                             : (double)p0.bc.omega[j]));
-  p.inv_bc2 = wave_uniform((float)(p0.bc.on ? 1.0 / (1.0 - pow_steps((double)p0.bc.beta2, s)) : 1.0));
+    if (j < p0.bc.n) p.w[j] = lane_value(w, j);
+  p.inv_bc2 = lane_value(w, p0.bc.n);
   return p;
 }
 
@@ -391,87 +533,109 @@ __device__ __forceinline__ void update_element(const StepParams& p, float sc, fl
   }
 }
 
+// The row that holds element e of a [K][P] buffer taken as a flat array:
+// e / P for 0 <= e < 2^40, rp = 1 / P in fp64.  e is exact
+// in fp64 and the product is off by less than one, so one correction each
+// way gives the quotient.
+__device__ __forceinline__ int64_t row_of(int64_t e, int64_t P, double rp) {
+  int64_t m = (int64_t)((double)e * rp);
+  if (m * P > e) --m;
+  if ((m + 1) * P <= e) ++m;
+  return m;
+}
+
 // One update of all elements of all replicas (Algorithm 1, 2 or 3 body).
+// The update is element-wise, so the [K][P] buffers are taken as flat arrays
+// of n = K P elements: every access starts at a multiple of V elements from
+// a 16-byte aligned base whatever P is, and only the clip factor needs the
+// row of an element.
 //   FORM       kAdam / kAdopt / kSgdm
 //   N          number of first moments
 //   XT, GT     storage of params / gradients (float or bf16)
-//   V, U       elements per vector slot, slots per thread per tile
+//   V          elements per thread
 //   NTM        bit 0: nontemporal loads, bit 1: nontemporal stores
 //   ORDER      ADOPT normalisation order (kPrev: v from before this step)
-//   B          threads per block
-//   C          elements per piece of the tile -> element map (tile_elem)
-//   WIN        which rows and ranges a workgroup's tiles cover:
-//              kWinOne       blockIdx.y = replica, tiles of the whole row;
-//              kWinHalves    blockIdx.y = replica, even workgroups take
-//                            [0, wlen) and odd ones [wlen, P);
-//              kWinPairs     blockIdx.y = m < ceil(K / 2), even workgroups
-//                            take row m and odd ones row m + ceil(K / 2).
-//              Each stream is then read at two places at once, half a row
-//              or half the replicas apart; measured on MI355X at 1.31B x 4
-//              (bare streams, same buffers): 79.5% of the HBM peak for one
-//              window, 80.0% for halves, 80.4% for replica pairs.
-template <int FORM, int N, typename XT, typename GT, int V, int U, int NTM, int ORDER, int B = kBlock, int C = 0,
-          int WIN = kWinOne>
+//   ROWS       clip factors: kNoScale, kTwoRows (rows of at least a wave's
+//              64 V elements, so a wave meets two rows at most) or kAnyRows
+//   B          threads of a workgroup
+// A wave's elements are one piece of the tile -> element map (tile_elem).
+// The launch limits the workgroups that a CU holds at once (resident_lds in
+// the host code): the HBM serves the fewest bytes that cover its latency
+// faster than all that the CUs could keep in flight.
+enum ScaleRows { kNoScale = 0, kTwoRows = 1, kAnyRows = 2 };
+
+template <int FORM, int N, typename XT, typename GT, int V, int NTM, int ORDER, int ROWS, int B>
 __global__ __launch_bounds__(B) void k_local_step(StepParams p0) {
   constexpr bool NTL = (NTM & 1) != 0, NTS = (NTM & 2) != 0;
+  constexpr int C = 64 * V;
 
-  for (int64_t tile = blockIdx.x; tile < p0.tiles; tile += gridDim.x) {
-    // the row m and the range [base, end) of it that this tile belongs to
-    const int64_t w = WIN == kWinOne ? 0 : (tile & 1);
-    const int64_t wt = WIN == kWinOne ? tile : (tile >> 1);
-    int64_t m = blockIdx.y, base = 0, end = p0.P;
-    if constexpr (WIN == kWinHalves) {
-      base = w * p0.wlen;
-      end = w == 0 ? p0.wlen : p0.P;
-    } else if constexpr (WIN == kWinPairs) {
-      m += w * (int64_t)gridDim.y;
-      if (m >= p0.replicas) continue;  // odd K: the last row has no partner
-    }
-    const int64_t row = m * p0.P;
-    XT* __restrict__ x = reinterpret_cast<XT*>(p0.x) + row;
-    const GT* __restrict__ g = reinterpret_cast<const GT*>(p0.g) + row;
-    float* __restrict__ u[N];
+  XT* x = reinterpret_cast<XT*>(p0.x);
+  const GT* g = reinterpret_cast<const GT*>(p0.g);
+  float* u[kMaxN];
 #pragma unroll
-    for (int j = 0; j < N; ++j) u[j] = p0.u[j] + row;
-    float* __restrict__ v = (FORM == kSgdm) ? nullptr : p0.v + row;
-    const float sc = (FORM != kAdopt && p0.scale != nullptr) ? load_uniform(p0.scale + m) : 1.0f;
-    float gv[U][V], xv[U][V], uv[U][N][V], vv[U][V];
+  for (int j = 0; j < kMaxN; ++j) u[j] = p0.u[j < N ? j : 0];
+  float* v = FORM != kSgdm ? p0.v : p0.u[0];
+  const int64_t total = p0.n;
+  in_sgprs(x, g, u[0], v);
+  if constexpr (N > 1) in_sgprs(u[1], u[2], u[3], v);
+
+  const int64_t tile = launch_tile();
+  // the tile's first element, and this thread's place after it
+  const int64_t base = tile_elem<B * V, C>(tile, 0);
+  const uint32_t o = (uint32_t)tile_elem<B * V, C>(0, (int)threadIdx.x * V);
+  const int32_t ow = __builtin_amdgcn_readfirstlane((int32_t)o);
+  const int32_t nw = left_in_row(base, total) - ow, n = left_in_row(base, total) - (int32_t)o;
+  x += base;
+  g += base;
+#pragma unroll
+  for (int j = 0; j < N; ++j) u[j] += base;
+  if constexpr (FORM != kSgdm) v += base;
+  // the wave's piece: whole (one uniform branch, so that the vector path has
+  // no merges with the other between its loads and its stores), or the last
+  // one of the buffers
+  auto piece = [&](auto full) {
+    constexpr bool F = decltype(full)::value;
+    float gv[V], xv[V], uv[N][V], vv[V];
     // issue every load of the tile before any arithmetic
+    load_n<F, GT, V, NTL>(g, o, n, gv);
+    load_n<F, XT, V, NTL>(x, o, n, xv);
 #pragma unroll
-    for (int k = 0; k < U; ++k) {
-      const int64_t e = base + tile_elem<B * V * U, C>(wt, (k * B + (int)threadIdx.x) * V);
-      if (e < end) {
-        load_v<GT, V, NTL>(g, e, gv[k]);
-        load_v<XT, V, NTL>(x, e, xv[k]);
-#pragma unroll
-        for (int j = 0; j < N; ++j) load_v<float, V, NTL>(u[j], e, uv[k][j]);
-        if constexpr (FORM != kSgdm) load_v<float, V, NTL>(v, e, vv[k]);
-      }
+    for (int j = 0; j < N; ++j) load_n<F, float, V, NTL>(u[j], o, n, uv[j]);
+    if constexpr (FORM != kSgdm) load_n<F, float, V, NTL>(v, o, n, vv);
+    // clip factors: s0 for the row of the wave's first element, s1 from
+    // `left` elements after this thread's first, where the next row starts
+    float s0 = 1.0f, s1 = 1.0f;
+    int32_t left = V;
+    if constexpr (ROWS == kTwoRows) {
+      const int32_t m = __builtin_amdgcn_readfirstlane((int32_t)row_of(base + ow, p0.P, p0.rp));
+      s0 = load_uniform(p0.scale + m);
+      s1 = load_uniform(p0.scale + (m + 1 < p0.replicas ? m + 1 : m));
+      left = left_in_row(base, (m + 1) * p0.P) - (int32_t)o;
     }
     // the step-dependent scalars after the loads are in flight (from the
     // device-side update number when there is one)
     const StepParams p = device_scalars(p0);
 #pragma unroll
-    for (int k = 0; k < U; ++k) {
-      const int64_t e = base + tile_elem<B * V * U, C>(wt, (k * B + (int)threadIdx.x) * V);
-      if (e >= end) continue;
+    for (int t = 0; t < V; ++t) {
+      float uu[N];
 #pragma unroll
-      for (int t = 0; t < V; ++t) {
-        float uu[N];
+      for (int j = 0; j < N; ++j) uu[j] = uv[j][t];
+      float vt = (FORM != kSgdm) ? vv[t] : 0.0f;
+      float sc = 1.0f;
+      if constexpr (ROWS == kTwoRows) sc = t < left ? s0 : s1;
+      if constexpr (ROWS == kAnyRows) sc = t < n ? p0.scale[row_of(base + o + t, p0.P, p0.rp)] : 1.0f;
+      update_element<FORM, N, ORDER>(p, sc, gv[t], xv[t], uu, vt);
 #pragma unroll
-        for (int j = 0; j < N; ++j) uu[j] = uv[k][j][t];
-        float vt = (FORM != kSgdm) ? vv[k][t] : 0.0f;
-        update_element<FORM, N, ORDER>(p, sc, gv[k][t], xv[k][t], uu, vt);
-#pragma unroll
-        for (int j = 0; j < N; ++j) uv[k][j][t] = uu[j];
-        if constexpr (FORM != kSgdm) vv[k][t] = vt;
-      }
-      store_v<XT, V, NTS>(x, e, xv[k]);
-#pragma unroll
-      for (int j = 0; j < N; ++j) store_v<float, V, NTS>(u[j], e, uv[k][j]);
-      if constexpr (FORM != kSgdm) store_v<float, V, NTS>(v, e, vv[k]);
+      for (int j = 0; j < N; ++j) uv[j][t] = uu[j];
+      if constexpr (FORM != kSgdm) vv[t] = vt;
     }
-  }
+    store_n<F, XT, V, NTS>(x, o, n, xv);
+#pragma unroll
+    for (int j = 0; j < N; ++j) store_n<F, float, V, NTS>(u[j], o, n, uv[j]);
+    if constexpr (FORM != kSgdm) store_n<F, float, V, NTS>(v, o, n, vv);
+  };
+  if (nw >= C) piece(BoolC<true>{});
+  else if (nw > 0) piece(BoolC<false>{});
 }
 
 // Value a state holds once stored: bf16 parameters are rounded.
@@ -644,15 +808,17 @@ void k_local_step_sync_waves(StepParams p0, uint32_t mask, int32_t K) {
     const bool in = e < p0.P;
     const int64_t r = (int64_t)m * p0.P + e;
     float val[NS][V];  // updated x, u^j, v of this lane's elements
+    float gv[V], uv[N][V];
     if (in) {
-      float gv[V], uv[N][V];
       load_v<GT, V, NTL>(g, r, gv);
       load_v<XT, V, NTL>(x, r, val[0]);
 #pragma unroll
       for (int j = 0; j < N; ++j) load_v<float, V, NTL>(p0.u[j], r, uv[j]);
       if constexpr (FORM != kSgdm) load_v<float, V, NTL>(p0.v, r, val[NS - 1]);
-      // the step-dependent scalars after the loads are in flight
-      const StepParams p = kEarly ? early : device_scalars(p0);
+    }
+    // the step-dependent scalars after the loads are in flight
+    const StepParams p = kEarly ? early : device_scalars(p0);
+    if (in) {
 #pragma unroll
       for (int t = 0; t < V; ++t) {
         float uu[N];

@@ -52,68 +52,49 @@ unsigned blocks(int64_t n4) {
   return (unsigned)(b < 8 ? 8 : b);
 }
 
-// The local step's memory traffic without its arithmetic: the loop of
-// k_local_step (same tile placement, 4-element slots, one slot per thread,
-// nontemporal loads and stores, the same windows per row) reading g, x,
-// u^1..u^N and v, and storing x, u^j and v back unchanged.  The store is
+// The local step's memory traffic without its arithmetic: the accesses of
+// k_local_step (flat buffers, same tile placement, 4-element slots, the same
+// workgroups and workgroups per CU, nontemporal loads and stores) reading g,
+// x, u^1..u^N and v, and storing x, u^j and v back unchanged.  The store is
 // kept by a comparison with `guard` (NaN: never true) that depends on every
 // loaded value, so no load is dropped and the buffers keep their contents.
-template <int N, bool HAS_V, typename XT, typename GT, int WIN>
-__global__ __launch_bounds__(mtdao::kBlock) void k_step_mix(mtdao::StepParams p, float guard) {
+template <int N, bool HAS_V, typename XT, typename GT, int B>
+__global__ __launch_bounds__(B) void k_step_mix(mtdao::StepParams p, float guard) {
   using namespace mtdao;
-  constexpr int V = 4, T = kBlock * V, C = 64 * V;
-  for (int64_t tile = blockIdx.x; tile < p.tiles; tile += gridDim.x) {
-    const int64_t w = tile & 1, wt = tile >> 1;
-    int64_t m = blockIdx.y, base = 0, end = p.P;
-    if constexpr (WIN == kWinHalves) {
-      base = w * p.wlen;
-      end = w == 0 ? p.wlen : p.P;
-    } else {
-      m += w * (int64_t)gridDim.y;
-      if (m >= p.replicas) continue;
-    }
-    const int64_t row = m * p.P;
-    XT* __restrict__ x = reinterpret_cast<XT*>(p.x) + row;
-    const GT* __restrict__ g = reinterpret_cast<const GT*>(p.g) + row;
-    const int64_t e = base + tile_elem<T, C>(wt, (int)threadIdx.x * V);
-    if (e >= end) continue;
-    float gv[V], xv[V], uv[N][V], vv[V];
-    load_v<GT, V, true>(g, e, gv);
-    load_v<XT, V, true>(x, e, xv);
+  constexpr int V = 4, T = B * V, C = 64 * V;
+  XT* __restrict__ x = reinterpret_cast<XT*>(p.x);
+  const GT* __restrict__ g = reinterpret_cast<const GT*>(p.g);
+  const int64_t e = tile_elem<T, C>(launch_tile(), (int)threadIdx.x * V);
+  if (e >= p.n) return;
+  float gv[V], xv[V], uv[N][V], vv[V];
+  load_v<GT, V, true>(g, e, gv);
+  load_v<XT, V, true>(x, e, xv);
 #pragma unroll
-    for (int j = 0; j < N; ++j) load_v<float, V, true>(p.u[j] + row, e, uv[j]);
-    if constexpr (HAS_V) load_v<float, V, true>(p.v + row, e, vv);
-    float sum = 0.0f;
+  for (int j = 0; j < N; ++j) load_v<float, V, true>(p.u[j], e, uv[j]);
+  if constexpr (HAS_V) load_v<float, V, true>(p.v, e, vv);
+  float sum = 0.0f;
 #pragma unroll
-    for (int t = 0; t < V; ++t) {
-      sum += gv[t] + xv[t];
+  for (int t = 0; t < V; ++t) {
+    sum += gv[t] + xv[t];
 #pragma unroll
-      for (int j = 0; j < N; ++j) sum += uv[j][t];
-      if constexpr (HAS_V) sum += vv[t];
-    }
-    if (sum == guard) xv[0] += 1.0f;
-    store_v<XT, V, true>(x, e, xv);
-#pragma unroll
-    for (int j = 0; j < N; ++j) store_v<float, V, true>(p.u[j] + row, e, uv[j]);
-    if constexpr (HAS_V) store_v<float, V, true>(p.v + row, e, vv);
+    for (int j = 0; j < N; ++j) sum += uv[j][t];
+    if constexpr (HAS_V) sum += vv[t];
   }
+  if (sum == guard) xv[0] += 1.0f;
+  store_v<XT, V, true>(x, e, xv);
+#pragma unroll
+  for (int j = 0; j < N; ++j) store_v<float, V, true>(p.u[j], e, uv[j]);
+  if constexpr (HAS_V) store_v<float, V, true>(p.v, e, vv);
 }
 
 template <int N, bool HAS_V, typename XT, typename GT>
 void launch_step_mix(mtdao::StepParams p, int32_t K, hipStream_t st) {
   using namespace mtdao;
-  constexpr int T = kBlock * 4, C = 256;
-  if (K > 1) {
-    p.tiles = 2 * tiles_for<T, C>(p.P);
-    hipLaunchKernelGGL((k_step_mix<N, HAS_V, XT, GT, kWinPairs>), dim3((unsigned)p.tiles, (K + 1) / 2),
-                       dim3(kBlock), 0, st, p, __builtin_nanf(""));
-  } else {
-    p.wlen = ((p.P + 1) / 2 + T - 1) / T * T;
-    if (p.wlen > p.P) p.wlen = p.P;
-    p.tiles = 2 * tiles_for<T, C>(p.wlen);
-    hipLaunchKernelGGL((k_step_mix<N, HAS_V, XT, GT, kWinHalves>), dim3((unsigned)p.tiles, K), dim3(kBlock), 0, st,
-                       p, __builtin_nanf(""));
-  }
+  constexpr StepLaunch L = step_launch((int)(sizeof(XT) + sizeof(GT)) + 4 * N + (HAS_V ? 4 : 0));
+  p.n = p.P * K;
+  const bool limit = p.n * L.bytes >= kResidentMin;
+  hipLaunchKernelGGL((k_step_mix<N, HAS_V, XT, GT, L.threads>), tile_grid(tiles_for<L.threads * 4, 256>(p.n)),
+                     dim3(L.threads), limit ? resident_lds(L.resident) : 0, st, p, __builtin_nanf(""));
 }
 
 }  // namespace
