@@ -2,18 +2,19 @@
 //
 // All kernels are streaming, HBM-bound passes: the local step reads x, g,
 // u^1..u^N, v once and writes x, u^1..u^N, v once per element (no MFMA:
-// there is no contraction).  Every thread owns V consecutive elements of
-// one replica row per vector slot, so loads and stores are 16-byte vector
-// accesses and a 64-lane wavefront moves 1 KiB per instruction; all loads
-// of a tile are issued before any of them is consumed.  Rows are
-// replica-major [K][P].  Two organisations:
-//   - one replica row per workgroup (the plain step, the norm pass, the
-//     thread-per-column kernels): blockIdx.y is the replica (the state,
-//     for the mean), blockIdx.x a tile of the row placed by tile_elem();
+// there is no contraction).  A lane owns V consecutive elements, so loads
+// and stores are 16-byte vector accesses (8-byte for bf16 in the step) and a
+// 64-lane wavefront moves 1 KiB per instruction; all loads of a tile are
+// issued before any of them is consumed.  Rows are replica-major [K][P] and
+// start at any element: vectors are aligned to their element only.  Three
+// organisations:
+//   - flat: the plain step takes the K P elements of each buffer as one
+//     array, as the update is element-wise;
 //   - one wavefront per replica (the fused step + sync, the mean, the
 //     diagnostics and Algorithm 4's step for 1 < K <= 16): a workgroup of
 //     K waves takes one piece of 64 V elements of every row, and values
-//     that must be averaged meet in LDS.
+//     that must be averaged meet in LDS;
+//   - one thread per column of all K rows (the same for K = 1 and K > 16).
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -82,8 +83,8 @@ __device__ __forceinline__ void in_sgprs(A*& a, B*& b, C*& c, D*& d) {
 // --------------------------------------------------- vector load / store
 //
 // load_v<T, V>(p, e, out): V consecutive elements starting at element e,
-// widened to fp32.  T = float, or uint16_t holding bf16 bit patterns.  V = 1 (scalar path for rows whose
-// length breaks 16-byte alignment), 4 or 8.
+// widened to fp32.  T = float, or uint16_t holding bf16 bit patterns.  V = 1
+// (the end of a row), 4 or 8.
 
 // (vector types go by alias: a deduced type would lose the alignment)
 template <bool NT, typename VT>
@@ -279,6 +280,27 @@ inline dim3 tile_grid(int64_t tiles, int32_t nz = 1) {
   return dim3((unsigned)(y == 1 ? tiles : maxx), (unsigned)y, (unsigned)nz);
 }
 
+// The piece of this workgroup in the wave-per-replica kernels, which take
+// one piece of every row.  group = 1: pieces in order, so the XCDs take one
+// in turn.  group = G > 1: each XCD takes G consecutive pieces with G
+// workgroups that follow one another on it.  Rows that do not start on
+// 128-byte lines share a line between neighbouring pieces; written from two
+// XCDs' L2 caches each half goes to memory by itself, so such rows take
+// G = 8 (row_group): 16.8M + 37 x 4 Adam with x due 610 -> 550 us, 30M + 1
+// x 8 ADOPT bf16 with all due 1665 -> 1494 us; G = 16 and 32 were equal.
+// Rows on whole lines take G = 1, which spreads the XCDs best (354M x 4 all
+// due 10.9 ms, G = 8 11.3 ms).  Pieces past the row have no elements.
+__device__ __forceinline__ int64_t group_piece(int32_t group) {
+  const int64_t t = launch_tile();
+  if (group == 1) return t;
+  return t / (8 * group) * (8 * group) + (t & 7) * group + (t >> 3) % group;
+}
+inline int32_t row_group(int64_t P) { return P % 64 == 0 ? 1 : 8; }
+inline dim3 group_grid(int64_t pieces, int32_t group, int32_t nz = 1) {
+  const int64_t span = group == 1 ? 1 : 8 * group;
+  return tile_grid((pieces + span - 1) / span * span, nz);
+}
+
 // Workgroups per CU of the streaming kernels.  Bytes in flight beyond what
 // covers the HBM's latency only spread the accesses over more DRAM pages:
 // about 40 KiB of loads per CU ran fastest for every mix of streams, against
@@ -291,6 +313,15 @@ inline dim3 tile_grid(int64_t tiles, int32_t nz = 1) {
 // 30.3 us, 352 MB 57.2 us against 59.2 us).
 constexpr int64_t kResidentMin = INT64_C(64) << 20;
 constexpr size_t resident_lds(int n) { return (size_t)(128 / n > 51 ? 51 : 128 / n) * 1280; }
+
+// Workgroups per CU of the fused step with one wave per replica, whose
+// barriers ask for more waves than the plain step: 12 waves, at least two
+// workgroups.  K > 8 has two by its size (one took 0.86 to 0.96 of the
+// rate).  Unlimited -> limited on the same buffers of an MI355X: K = 4 Adam
+// N = 3 with x due 16.8M 515 -> 473 us, all due 354M 11.39 -> 10.55 ms;
+// K = 6 with x due 40M 1947 -> 1815 us; K = 8 ADOPT bf16 all due 60M
+// 2652 -> 2471 us; K = 2 all due 60M 871 -> 847 us.
+constexpr int wave_resident(int K) { return 12 / K > 2 ? 12 / K : 2; }
 
 // The local step's workgroups for `bytes` loaded per element (four elements
 // per lane): two waves each, for steps of the limit that are fine enough,
@@ -342,23 +373,39 @@ __device__ __forceinline__ void outer_step(const OuterParams& o, int64_t e, floa
   store_v<float, V, false>(o.mom, e, b);
 }
 
-// The OuterOpt over one piece of 64 V elements whose means sit in LDS,
-// means[t * 64 + l] = element l V + t of the piece starting at element e0
-// (the layout of the wave-per-replica kernels).  Wave m of the K takes
-// every K-th run of 64 consecutive elements, so the fp32 outer parameters
-// and momentum are read and written in accesses that are contiguous across
-// the lanes of a wave (the column-by-wave order of the mean phase would
-// put them 16 bytes apart).  Each element gets exactly outer_step's update.
-template <int V>
-__device__ __forceinline__ void outer_step_piece(const OuterParams& o, int64_t e0, int64_t P, int32_t K, int32_t m,
-                                                 int32_t lane, float* means) {
-  for (int j = m * 64 + lane; j < 64 * V; j += 64 * K) {
-    if (e0 + j >= P) continue;
-    const int l = j / V, t = j % V;
-    float a[1] = {means[t * 64 + l]};
-    outer_step<1>(o, e0 + j, a);
-    means[t * 64 + l] = a[0];
+// The same over the n elements of a row's last piece (FULL: all V).
+template <bool FULL, int V>
+__device__ __forceinline__ void outer_step_n(const OuterParams& o, int64_t e, int32_t n, float (&xbar)[V]) {
+  if constexpr (FULL) {
+    outer_step<V>(o, e, xbar);
+  } else {
+#pragma unroll
+    for (int t = 0; t < V; ++t)
+      if (t < n) {
+        float a[1] = {xbar[t]};
+        outer_step<1>(o, e + t, a);
+        xbar[t] = a[0];
+      }
   }
+}
+
+// The outer parameters and momentum of the elements that a thread averages,
+// loaded with the tile: loaded after the mean, their latency was part of
+// every workgroup's chain of barriers.  U elements per thread at most.
+template <int U>
+struct OuterAhead {
+  float xo[U], mom[U];
+};
+
+// outer_step's update of element e with its inputs already loaded.
+__device__ __forceinline__ float outer_element(const OuterParams& o, int64_t e, float xo, float mom, float xbar) {
+#pragma clang fp contract(off)
+  const float d = xo - xbar;
+  const float b = __builtin_fmaf(o.mu, mom, d);
+  xo = __builtin_fmaf(-o.lr, __builtin_fmaf(o.mu, b, d), xo);
+  o.xo[e] = xo;
+  o.mom[e] = b;
+  return xo;
 }
 
 // ------------------------------------------------------------ local step
@@ -419,10 +466,10 @@ struct StepParams {
   float* v;                // [K][P] second moment (Adam, ADOPT)
   const float* scale;      // [K] global-norm clip factors, or nullptr
   int64_t P;               // row length
-  int64_t tiles;           // tiles of the launch
   int64_t n;               // k_local_step: K P, elements of a state
   double rp;               // 1 / P
   int32_t replicas;        // K
+  int32_t group;           // wave-per-replica kernels: group_piece
   float beta[kMaxN];       // beta_{1,j}
   float omb[kMaxN];        // 1 - beta_{1,j}
   float w[kMaxN];          // omega_j (times 1/(1 - beta_{1,j}^s) for bias-corrected Adam)
@@ -665,7 +712,7 @@ __device__ __forceinline__ float mean_of(float s0, double d, double rk) {
 // k_replica_mean, so both paths give bit-identical results -- then writes
 // that mean to all K rows.  The separate mean pass (2 K sizeof(T) bytes
 // per element per due state) disappears.
-template <int FORM, int N, typename XT, typename GT, int V, int NTM, int ORDER, int C = 0>
+template <int FORM, int N, typename XT, typename GT, int V, int NTM, int ORDER>
 __global__ __launch_bounds__(kBlock) void k_local_step_sync(StepParams p0, uint32_t mask, int32_t K) {
   const StepParams p = device_scalars(p0);
   constexpr bool NTL = (NTM & 1) != 0, NTS = (NTM & 2) != 0;
@@ -678,9 +725,12 @@ __global__ __launch_bounds__(kBlock) void k_local_step_sync(StepParams p0, uint3
   const GT* __restrict__ g = reinterpret_cast<const GT*>(p.g);
   const double rk = 1.0 / (double)K;
 
-  for (int64_t tile = blockIdx.x; tile < p.tiles; tile += gridDim.x) {
-    const int64_t e = tile_elem<kBlock * V, C>(tile, (int)threadIdx.x * V);
-    if (e >= p.P) continue;
+  // a wave's elements are one piece of the tile
+  const int64_t base = tile_elem<kBlock * V, 64 * V>(launch_tile(), 0);
+  const uint32_t o = (uint32_t)tile_elem<kBlock * V, 64 * V>(0, (int)threadIdx.x * V);
+  const int32_t n = left_in_row(base, p.P) - (int32_t)o, nw = __builtin_amdgcn_readfirstlane(n);
+  auto piece = [&](auto full) {
+    constexpr bool F = decltype(full)::value;
     float x0[V], u0[N][V], v0[V];
     double dx[V], du[N][V], dv[V];
 #pragma unroll
@@ -691,13 +741,13 @@ __global__ __launch_bounds__(kBlock) void k_local_step_sync(StepParams p0, uint3
       for (int j = 0; j < N; ++j) du[j][t] = 0.0;
     }
     for (int32_t m = 0; m < K; ++m) {
-      const int64_t r = (int64_t)m * p.P + e;
+      const int64_t r = (int64_t)m * p.P + base;
       float gv[V], xv[V], uv[N][V], vv[V];
-      load_v<GT, V, NTL>(g, r, gv);
-      load_v<XT, V, NTL>(x, r, xv);
+      load_n<F, GT, V, NTL>(g + r, o, n, gv);
+      load_n<F, XT, V, NTL>(x + r, o, n, xv);
 #pragma unroll
-      for (int j = 0; j < N; ++j) load_v<float, V, NTL>(p.u[j], r, uv[j]);
-      if constexpr (FORM != kSgdm) load_v<float, V, NTL>(p.v, r, vv);
+      for (int j = 0; j < N; ++j) load_n<F, float, V, NTL>(p.u[j] + r, o, n, uv[j]);
+      if constexpr (FORM != kSgdm) load_n<F, float, V, NTL>(p.v + r, o, n, vv);
       const float sc = (FORM != kAdopt && p.scale != nullptr) ? load_uniform(p.scale + m) : 1.0f;
 #pragma unroll
       for (int t = 0; t < V; ++t) {
@@ -719,7 +769,7 @@ __global__ __launch_bounds__(kBlock) void k_local_step_sync(StepParams p0, uint3
           else mean_add(dx[t], xv[t], x0[t]);
         }
       } else {
-        store_v<XT, V, NTS>(x, r, xv);
+        store_n<F, XT, V, NTS>(x + r, o, n, xv);
       }
 #pragma unroll
       for (int j = 0; j < N; ++j) {
@@ -730,7 +780,7 @@ __global__ __launch_bounds__(kBlock) void k_local_step_sync(StepParams p0, uint3
             else mean_add(du[j][t], uv[j][t], u0[j][t]);
           }
         } else {
-          store_v<float, V, NTS>(p.u[j], r, uv[j]);
+          store_n<F, float, V, NTS>(p.u[j] + r, o, n, uv[j]);
         }
       }
       if constexpr (FORM != kSgdm) {
@@ -741,7 +791,7 @@ __global__ __launch_bounds__(kBlock) void k_local_step_sync(StepParams p0, uint3
             else mean_add(dv[t], vv[t], v0[t]);
           }
         } else {
-          store_v<float, V, NTS>(p.v, r, vv);
+          store_n<F, float, V, NTS>(p.v + r, o, n, vv);
         }
       }
     }
@@ -749,42 +799,187 @@ __global__ __launch_bounds__(kBlock) void k_local_step_sync(StepParams p0, uint3
     if (sync_x) {
 #pragma unroll
       for (int t = 0; t < V; ++t) x0[t] = mean_of(x0[t], dx[t], rk);
-      outer_step<V>(p.outer, e, x0);
-      for (int32_t m = 0; m < K; ++m) store_v<XT, V, NTS>(x, (int64_t)m * p.P + e, x0);
+      outer_step_n<F, V>(p.outer, base + o, n, x0);
+      for (int32_t m = 0; m < K; ++m) store_n<F, XT, V, NTS>(x + (int64_t)m * p.P + base, o, n, x0);
     }
 #pragma unroll
     for (int j = 0; j < N; ++j) {
       if (!sync_u[j]) continue;
 #pragma unroll
       for (int t = 0; t < V; ++t) u0[j][t] = mean_of(u0[j][t], du[j][t], rk);
-      for (int32_t m = 0; m < K; ++m) store_v<float, V, NTS>(p.u[j], (int64_t)m * p.P + e, u0[j]);
+      for (int32_t m = 0; m < K; ++m) store_n<F, float, V, NTS>(p.u[j] + (int64_t)m * p.P + base, o, n, u0[j]);
     }
     if constexpr (FORM != kSgdm) {
       if (sync_v) {
 #pragma unroll
         for (int t = 0; t < V; ++t) v0[t] = mean_of(v0[t], dv[t], rk);
-        for (int32_t m = 0; m < K; ++m) store_v<float, V, NTS>(p.v, (int64_t)m * p.P + e, v0);
+        for (int32_t m = 0; m < K; ++m) store_n<F, float, V, NTS>(p.v + (int64_t)m * p.P + base, o, n, v0);
       }
+    }
+  };
+  if (nw >= 64 * V) piece(BoolC<true>{});
+  else if (nw > 0) piece(BoolC<false>{});
+}
+
+// The wave-per-replica kernels (1 < K <= kWaveMaxK): a workgroup of K waves
+// (or K / R, R rows per wave) takes one piece of 64 V elements of every row,
+// so every row has its own loads in flight, and values to be averaged meet
+// in LDS as [K][64 V] floats in element order.
+constexpr int kWaveMaxK = 16;
+constexpr int kPieceMaxU = 2;  // elements of a 4-element-per-lane piece per thread at K = 2
+
+// Averages `states` stages of E elements that lie back to back in LDS, each
+// [K][E]: element c's mean, in replica order with mean_add and mean_of,
+// replaces its row 0 value.  Threads take (stage, element) pairs in turn, so
+// all waves of the workgroup share the work.  With `outer` (and `ahead`
+// loaded by outer_ahead) stage 0 is x and takes the OuterOpt.
+template <int E, int U>
+__device__ __forceinline__ void average_stages(float* lds, int32_t K, int32_t states, int32_t in_row, double rk,
+                                               const OuterParams& o, bool outer, const OuterAhead<U>& ahead,
+                                               int64_t e0) {
+  auto mean = [&](int32_t j) {
+    float* q = lds + (j / E) * (K * E) + j % E;
+    const float s0 = q[0];
+    double d = 0.0;
+#pragma unroll 4
+    for (int32_t m = 1; m < K; ++m) mean_add(d, q[m * E], s0);
+    return mean_of(s0, d, rk);
+  };
+  int32_t j = threadIdx.x;
+  if (outer) {
+#pragma unroll
+    for (int i = 0; i < U; ++i) {
+      if (j < E) {
+        if (j < in_row) lds[j] = outer_element(o, e0 + j, ahead.xo[i], ahead.mom[i], mean(j));
+        j += blockDim.x;
+      }
+    }
+  }
+  for (; j < states * E; j += blockDim.x)
+    if (j % E < in_row) lds[(j / E) * (K * E) + j % E] = mean(j);
+}
+
+// The outer inputs of elements e0 + threadIdx.x, + blockDim.x, ... below E.
+template <int E, int U>
+__device__ __forceinline__ void outer_ahead(const OuterParams& o, int64_t e0, int32_t in_row, OuterAhead<U>& a) {
+#pragma unroll
+  for (int i = 0; i < U; ++i) {
+    const int32_t j = (int32_t)threadIdx.x + i * (int32_t)blockDim.x;
+    if (j < E && j < in_row) {
+      a.xo[i] = o.xo[e0 + j];
+      a.mom[i] = o.mom[e0 + j];
     }
   }
 }
 
-// The same fused step + mean with one wavefront per replica (blockDim =
-// 64 K, 1 < K <= kWaveMaxK): lane l of wave m updates elements
-// [e, e + V) of replica m, e = tile 64 V + l V, exactly like the plain step,
-// so every replica keeps its own loads in flight.  For each due state the
-// updated values pass through LDS; the mean of column t of the tile is
-// formed by wave t mod K as S^0 + (sum_{m>=1}(S^m - S^0)) / K in replica
-// order (the arithmetic of k_replica_mean, bit for bit), the OuterOpt is
-// applied to x element by element, and every wave stores the mean to its
-// row.  Barriers are reached by all threads, also in the row tail.  The
-// register budget is held to 8 waves per SIMD, so two 16-wave workgroups
-// share a CU and one's mean phase overlaps the other's streaming.
-constexpr int kWaveMaxK = 16;
+// V floats at p in LDS, 16-byte aligned.
+typedef float lds_f32x4 __attribute__((ext_vector_type(4)));
+template <int V>
+__device__ __forceinline__ void lds_put(float* p, const float (&a)[V]) {
+#pragma unroll
+  for (int k = 0; k < V / 4; ++k)
+    reinterpret_cast<lds_f32x4*>(p)[k] = lds_f32x4{a[4 * k], a[4 * k + 1], a[4 * k + 2], a[4 * k + 3]};
+}
+template <int V>
+__device__ __forceinline__ void lds_get(const float* p, float (&a)[V]) {
+#pragma unroll
+  for (int k = 0; k < V / 4; ++k) {
+    const lds_f32x4 q = reinterpret_cast<const lds_f32x4*>(p)[k];
+    a[4 * k] = q.x; a[4 * k + 1] = q.y; a[4 * k + 2] = q.z; a[4 * k + 3] = q.w;
+  }
+}
 
+// The fused step + mean with one wavefront per replica (blockDim = 64 K):
+// lane l of wave m updates elements [4 l, 4 l + 4) of its piece of row m
+// exactly like the plain step.  States not due are stored at once; the due
+// ones are staged in LDS together (dynamic LDS of K * 64 V floats per due
+// state), averaged by all waves between two barriers, and every wave stores
+// the means to its row.  Every thread reaches the barriers, also in the last
+// piece of a row.
 template <int FORM, int N, typename XT, typename GT, int V, int NTM, int ORDER>
 __global__ __launch_bounds__(64 * kWaveMaxK) __attribute__((amdgpu_waves_per_eu(8)))
 void k_local_step_sync_waves(StepParams p0, uint32_t mask, int32_t K) {
+  constexpr bool NTL = (NTM & 1) != 0, NTS = (NTM & 2) != 0;
+  constexpr int NS = 2 + N, E = 64 * V;  // x, u^1..u^N, v
+  extern __shared__ __align__(16) float stage[];
+  const int32_t m = __builtin_amdgcn_readfirstlane((int32_t)(threadIdx.x >> 6));
+  const int64_t e0 = group_piece(p0.group) * E, row = (int64_t)m * p0.P + e0;
+  const uint32_t o = (threadIdx.x & 63) * V;
+  const int32_t in_row = left_in_row(e0, p0.P), n = in_row - (int32_t)o;
+  XT* x = reinterpret_cast<XT*>(p0.x) + row;
+  const GT* g = reinterpret_cast<const GT*>(p0.g) + row;
+  float* u[N];
+#pragma unroll
+  for (int j = 0; j < N; ++j) u[j] = p0.u[j] + row;
+  float* v = FORM != kSgdm ? p0.v + row : nullptr;
+
+  auto piece = [&](auto full) {
+    constexpr bool F = decltype(full)::value;
+    float gv[V], val[NS][V];  // x, u^j, v of this lane's elements
+    load_n<F, GT, V, NTL>(g, o, n, gv);
+    load_n<F, XT, V, NTL>(x, o, n, val[0]);
+#pragma unroll
+    for (int j = 0; j < N; ++j) load_n<F, float, V, NTL>(u[j], o, n, val[1 + j]);
+    if constexpr (FORM != kSgdm) load_n<F, float, V, NTL>(v, o, n, val[NS - 1]);
+    const bool outer = (mask & 1u) != 0 && p0.outer.xo != nullptr;
+    OuterAhead<kPieceMaxU> ahead;
+    if (outer) outer_ahead<E>(p0.outer, e0, in_row, ahead);
+    const float sc = (FORM != kAdopt && p0.scale != nullptr) ? load_uniform(p0.scale + m) : 1.0f;
+    // the step-dependent scalars after the loads are in flight
+    const StepParams p = device_scalars(p0);
+#pragma unroll
+    for (int t = 0; t < V; ++t) {
+      float uu[N];
+#pragma unroll
+      for (int j = 0; j < N; ++j) uu[j] = val[1 + j][t];
+      float vt = (FORM != kSgdm) ? val[NS - 1][t] : 0.0f;
+      update_element<FORM, N, ORDER>(p, sc, gv[t], val[0][t], uu, vt);
+      val[0][t] = as_stored<XT>(val[0][t]);
+#pragma unroll
+      for (int j = 0; j < N; ++j) val[1 + j][t] = uu[j];
+      val[NS - 1][t] = vt;
+    }
+    auto put = [&](int k, const float (&a)[V]) {
+      if (k == 0) store_n<F, XT, V, NTS>(x, o, n, a);
+      else if (k == NS - 1) store_n<F, float, V, NTS>(v, o, n, a);
+      else store_n<F, float, V, NTS>(u[k - 1 < N ? k - 1 : 0], o, n, a);
+    };
+    int32_t due = 0;
+#pragma unroll
+    for (int k = 0; k < NS; ++k) {
+      if (FORM == kSgdm && k == NS - 1) continue;
+      if ((mask >> k) & 1u) lds_put<V>(stage + (due++ * K + m) * E + o, val[k]);
+      else put(k, val[k]);
+    }
+    __syncthreads();
+    average_stages<E>(stage, K, due, in_row, 1.0 / (double)K, p0.outer, outer, ahead, e0);
+    __syncthreads();
+    due = 0;
+#pragma unroll
+    for (int k = 0; k < NS; ++k) {
+      if (FORM == kSgdm && k == NS - 1) continue;
+      if (!((mask >> k) & 1u)) continue;
+      float mean[V];
+      lds_get<V>(stage + due++ * K * E + o, mean);
+      put(k, mean);
+    }
+  };
+  if (in_row >= E) piece(BoolC<true>{});
+  else piece(BoolC<false>{});
+}
+
+// The same step with one exchange per due state: each is staged (column t of
+// the piece at [t][lane]), averaged by waves t mod K and stored before the
+// next is.  For K > 8 and row lengths that are a multiple of V, where the
+// staging of all due states together ran slower: the two 16-wave workgroups
+// of a CU cannot be fewer, and holding every state back until the one
+// exchange bunches their stores (SGDM N = 2, K = 16, all due, 60M: 4.89 ms,
+// staged together 4.96 ms; with x due, Adam N = 3, 20M: 2.70 against
+// 2.75 ms).  Other lengths take the kernel above (16M + 1: 1.65 ms, against
+// 2.72 ms for one element per lane).
+template <int FORM, int N, typename XT, typename GT, int V, int NTM, int ORDER>
+__global__ __launch_bounds__(64 * kWaveMaxK) __attribute__((amdgpu_waves_per_eu(8)))
+void k_local_step_sync_waves_rounds(StepParams p0, uint32_t mask, int32_t K) {
   constexpr bool NTL = (NTM & 1) != 0, NTS = (NTM & 2) != 0;
   // The device-side update number's scalars take a few dozen fp64
   // operations.  Formed after a tile's loads are issued, their latency is
@@ -803,72 +998,78 @@ void k_local_step_sync_waves(StepParams p0, uint32_t mask, int32_t K) {
   const float sc =
       (FORM != kAdopt && p0.scale != nullptr) ? load_uniform(p0.scale + __builtin_amdgcn_readfirstlane(m)) : 1.0f;
 
-  for (int64_t tile = blockIdx.x; tile < p0.tiles; tile += gridDim.x) {
-    const int64_t e = tile * (int64_t)(64 * V) + (int64_t)lane * V;
-    const bool in = e < p0.P;
-    const int64_t r = (int64_t)m * p0.P + e;
-    float val[NS][V];  // updated x, u^j, v of this lane's elements
-    float gv[V], uv[N][V];
-    if (in) {
-      load_v<GT, V, NTL>(g, r, gv);
-      load_v<XT, V, NTL>(x, r, val[0]);
+  const int64_t tile = launch_tile();
+  const int64_t e = tile * (int64_t)(64 * V) + (int64_t)lane * V;
+  const bool in = e < p0.P;
+  const int64_t r = (int64_t)m * p0.P + e;
+  float val[NS][V];  // updated x, u^j, v of this lane's elements
+  float gv[V], uv[N][V];
+  if (in) {
+    load_v<GT, V, NTL>(g, r, gv);
+    load_v<XT, V, NTL>(x, r, val[0]);
 #pragma unroll
-      for (int j = 0; j < N; ++j) load_v<float, V, NTL>(p0.u[j], r, uv[j]);
-      if constexpr (FORM != kSgdm) load_v<float, V, NTL>(p0.v, r, val[NS - 1]);
+    for (int j = 0; j < N; ++j) load_v<float, V, NTL>(p0.u[j], r, uv[j]);
+    if constexpr (FORM != kSgdm) load_v<float, V, NTL>(p0.v, r, val[NS - 1]);
+  }
+  // the step-dependent scalars after the loads are in flight
+  const StepParams p = kEarly ? early : device_scalars(p0);
+  if (in) {
+#pragma unroll
+    for (int t = 0; t < V; ++t) {
+      float uu[N];
+#pragma unroll
+      for (int j = 0; j < N; ++j) uu[j] = uv[j][t];
+      float vt = (FORM != kSgdm) ? val[NS - 1][t] : 0.0f;
+      update_element<FORM, N, ORDER>(p, sc, gv[t], val[0][t], uu, vt);
+      val[0][t] = as_stored<XT>(val[0][t]);
+#pragma unroll
+      for (int j = 0; j < N; ++j) val[1 + j][t] = uu[j];
+      val[NS - 1][t] = vt;
     }
-    // the step-dependent scalars after the loads are in flight
-    const StepParams p = kEarly ? early : device_scalars(p0);
-    if (in) {
+  }
 #pragma unroll
-      for (int t = 0; t < V; ++t) {
-        float uu[N];
-#pragma unroll
-        for (int j = 0; j < N; ++j) uu[j] = uv[j][t];
-        float vt = (FORM != kSgdm) ? val[NS - 1][t] : 0.0f;
-        update_element<FORM, N, ORDER>(p, sc, gv[t], val[0][t], uu, vt);
-        val[0][t] = as_stored<XT>(val[0][t]);
-#pragma unroll
-        for (int j = 0; j < N; ++j) val[1 + j][t] = uu[j];
-        val[NS - 1][t] = vt;
-      }
+  for (int k = 0; k < NS; ++k) {
+    if (FORM == kSgdm && k == NS - 1) continue;
+    const bool due = ((mask >> k) & 1u) != 0;
+    if (!due) {
+      if (!in) continue;
+      if (k == 0) store_v<XT, V, NTS>(x, r, val[0]);
+      else if (k == NS - 1) store_v<float, V, NTS>(p0.v, r, val[k]);
+      else store_v<float, V, NTS>(p0.u[k - 1], r, val[k]);
+      continue;
     }
 #pragma unroll
-    for (int k = 0; k < NS; ++k) {
-      if (FORM == kSgdm && k == NS - 1) continue;
-      const bool due = ((mask >> k) & 1u) != 0;
-      if (!due) {
-        if (!in) continue;
-        if (k == 0) store_v<XT, V, NTS>(x, r, val[0]);
-        else if (k == NS - 1) store_v<float, V, NTS>(p0.v, r, val[k]);
-        else store_v<float, V, NTS>(p0.u[k - 1], r, val[k]);
-        continue;
-      }
-#pragma unroll
-      for (int t = 0; t < V; ++t) lds[m][t * 64 + lane] = val[k][t];
-      __syncthreads();
-      // column t (element e + t of every lane) is averaged by wave t mod K
-      for (int t = m; in && t < V; t += K) {
-        const float s0 = lds[0][t * 64 + lane];
-        double d = 0.0;
+    for (int t = 0; t < V; ++t) lds[m][t * 64 + lane] = val[k][t];
+    __syncthreads();
+    // column t (element e + t of every lane) is averaged by wave t mod K
+    for (int t = m; in && t < V; t += K) {
+      const float s0 = lds[0][t * 64 + lane];
+      double d = 0.0;
 #pragma unroll 4
-        for (int32_t q = 1; q < K; ++q) mean_add(d, lds[q][t * 64 + lane], s0);
-        lds[0][t * 64 + lane] = mean_of(s0, d, rk);
-      }
-      __syncthreads();
-      if (k == 0 && p0.outer.xo != nullptr) {
-        outer_step_piece<V>(p0.outer, tile * (int64_t)(64 * V), p0.P, K, m, lane, &lds[0][0]);
-        __syncthreads();
-      }
-      if (in) {
-        float mean[V];
-#pragma unroll
-        for (int t = 0; t < V; ++t) mean[t] = lds[0][t * 64 + lane];
-        if (k == 0) store_v<XT, V, NTS>(x, r, mean);
-        else if (k == NS - 1) store_v<float, V, NTS>(p0.v, r, mean);
-        else store_v<float, V, NTS>(p0.u[k - 1], r, mean);
+      for (int32_t q = 1; q < K; ++q) mean_add(d, lds[q][t * 64 + lane], s0);
+      lds[0][t * 64 + lane] = mean_of(s0, d, rk);
+    }
+    __syncthreads();
+    if (k == 0 && p0.outer.xo != nullptr) {
+      // run j of 64 consecutive elements to wave j mod K
+      const int64_t e0 = tile * (int64_t)(64 * V);
+      for (int j = m * 64 + lane; j < 64 * V; j += 64 * K) {
+        if (e0 + j >= p0.P) continue;
+        float a[1] = {lds[0][(j % V) * 64 + j / V]};
+        outer_step<1>(p0.outer, e0 + j, a);
+        lds[0][(j % V) * 64 + j / V] = a[0];
       }
       __syncthreads();
     }
+    if (in) {
+      float mean[V];
+#pragma unroll
+      for (int t = 0; t < V; ++t) mean[t] = lds[0][t * 64 + lane];
+      if (k == 0) store_v<XT, V, NTS>(x, r, mean);
+      else if (k == NS - 1) store_v<float, V, NTS>(p0.v, r, mean);
+      else store_v<float, V, NTS>(p0.u[k - 1], r, mean);
+    }
+    __syncthreads();
   }
 }
 
@@ -879,7 +1080,7 @@ void k_local_step_sync_waves(StepParams p0, uint32_t mask, int32_t K) {
 // pass 1 updates every replica's moments and stores the ones not due (the
 // same thread reloads them in pass 2) and the means of the due ones; pass 2
 // forms each replica's direction and updates x.
-template <int N, typename XT, typename GT, int V, int NTM, int C = 0>
+template <int N, typename XT, typename GT, int V, int NTM>
 __global__ __launch_bounds__(kBlock) void k_sgdm_averaged_momenta(StepParams p0, uint32_t mask, int32_t K) {
 #pragma clang fp contract(off)
   const StepParams p = device_scalars(p0);
@@ -892,9 +1093,12 @@ __global__ __launch_bounds__(kBlock) void k_sgdm_averaged_momenta(StepParams p0,
   const GT* __restrict__ g = reinterpret_cast<const GT*>(p.g);
   const double rk = 1.0 / (double)K;
 
-  for (int64_t tile = blockIdx.x; tile < p.tiles; tile += gridDim.x) {
-    const int64_t e = tile_elem<kBlock * V, C>(tile, (int)threadIdx.x * V);
-    if (e >= p.P) continue;
+  // a wave's elements are one piece of the tile
+  const int64_t base = tile_elem<kBlock * V, 64 * V>(launch_tile(), 0);
+  const uint32_t o = (uint32_t)tile_elem<kBlock * V, 64 * V>(0, (int)threadIdx.x * V);
+  const int32_t n = left_in_row(base, p.P) - (int32_t)o, nw = __builtin_amdgcn_readfirstlane(n);
+  auto piece = [&](auto full) {
+    constexpr bool F = decltype(full)::value;
     // pass 1: u^j of every replica; due ones become their replica mean
     float u0[N][V];
     double du[N][V];
@@ -903,11 +1107,11 @@ __global__ __launch_bounds__(kBlock) void k_sgdm_averaged_momenta(StepParams p0,
 #pragma unroll
       for (int t = 0; t < V; ++t) du[j][t] = 0.0;
     for (int32_t m = 0; m < K; ++m) {
-      const int64_t r = (int64_t)m * p.P + e;
+      const int64_t r = (int64_t)m * p.P + base;
       float gv[V], uv[N][V];
-      load_v<GT, V, NTL>(g, r, gv);
+      load_n<F, GT, V, NTL>(g + r, o, n, gv);
 #pragma unroll
-      for (int j = 0; j < N; ++j) load_v<float, V, NTL>(p.u[j], r, uv[j]);
+      for (int j = 0; j < N; ++j) load_n<F, float, V, NTL>(p.u[j] + r, o, n, uv[j]);
       const float sc = p.scale != nullptr ? load_uniform(p.scale + m) : 1.0f;
 #pragma unroll
       for (int t = 0; t < V; ++t) {
@@ -924,7 +1128,7 @@ __global__ __launch_bounds__(kBlock) void k_sgdm_averaged_momenta(StepParams p0,
             else mean_add(du[j][t], uv[j][t], u0[j][t]);
           }
         } else {
-          store_v<float, V, false>(p.u[j], r, uv[j]);
+          store_n<F, float, V, false>(p.u[j] + r, o, n, uv[j]);
         }
       }
     }
@@ -933,7 +1137,7 @@ __global__ __launch_bounds__(kBlock) void k_sgdm_averaged_momenta(StepParams p0,
       if (!sync_u[j]) continue;
 #pragma unroll
       for (int t = 0; t < V; ++t) u0[j][t] = mean_of(u0[j][t], du[j][t], rk);
-      for (int32_t m = 0; m < K; ++m) store_v<float, V, NTS>(p.u[j], (int64_t)m * p.P + e, u0[j]);
+      for (int32_t m = 0; m < K; ++m) store_n<F, float, V, NTS>(p.u[j] + (int64_t)m * p.P + base, o, n, u0[j]);
     }
     // pass 2: direction with the averaged (due) or local (not due) moments
     float x0[V];
@@ -941,17 +1145,17 @@ __global__ __launch_bounds__(kBlock) void k_sgdm_averaged_momenta(StepParams p0,
 #pragma unroll
     for (int t = 0; t < V; ++t) dx[t] = 0.0;
     for (int32_t m = 0; m < K; ++m) {
-      const int64_t r = (int64_t)m * p.P + e;
+      const int64_t r = (int64_t)m * p.P + base;
       float gv[V], xv[V], uv[N][V];
-      load_v<GT, V, NTL>(g, r, gv);
-      load_v<XT, V, NTL>(x, r, xv);
+      load_n<F, GT, V, NTL>(g + r, o, n, gv);
+      load_n<F, XT, V, NTL>(x + r, o, n, xv);
 #pragma unroll
       for (int j = 0; j < N; ++j) {
         if (sync_u[j]) {
 #pragma unroll
           for (int t = 0; t < V; ++t) uv[j][t] = u0[j][t];
         } else {
-          load_v<float, V, false>(p.u[j], r, uv[j]);
+          load_n<F, float, V, false>(p.u[j] + r, o, n, uv[j]);
         }
       }
       const float sc = p.scale != nullptr ? load_uniform(p.scale + m) : 1.0f;
@@ -970,85 +1174,70 @@ __global__ __launch_bounds__(kBlock) void k_sgdm_averaged_momenta(StepParams p0,
           else mean_add(dx[t], xv[t], x0[t]);
         }
       } else {
-        store_v<XT, V, NTS>(x, r, xv);
+        store_n<F, XT, V, NTS>(x + r, o, n, xv);
       }
     }
     if (sync_x) {
 #pragma unroll
       for (int t = 0; t < V; ++t) x0[t] = mean_of(x0[t], dx[t], rk);
-      for (int32_t m = 0; m < K; ++m) store_v<XT, V, NTS>(x, (int64_t)m * p.P + e, x0);
+      for (int32_t m = 0; m < K; ++m) store_n<F, XT, V, NTS>(x + (int64_t)m * p.P + base, o, n, x0);
     }
-  }
+  };
+  if (nw >= 64 * V) piece(BoolC<true>{});
+  else if (nw > 0) piece(BoolC<false>{});
 }
 
 // The same step with one wavefront per replica (blockDim = 64 K,
 // 1 < K <= kWaveMaxK), in one pass: wave m loads g, x and every u^j of
-// replica m once, updates its moments, and each due moment meets its
-// replicas' values in LDS, where column t is averaged by wave t mod K (the
-// mean_add / mean_of order of every averaging kernel) and read back by
-// every wave before the direction uses it; x is updated and, when due,
-// averaged the same way.  The values equal k_sgdm_averaged_momenta's bit
-// for bit; that kernel re-reads g (and the moments not due) in its second
-// pass.  Barriers are reached by every thread, also in the row tail.
+// replica m once and updates its moments; the due ones are staged in LDS
+// together, averaged and read back by every wave before the direction uses
+// them; x is updated and, when due, averaged the same way.  The values equal
+// k_sgdm_averaged_momenta's bit for bit; that kernel re-reads g (and the
+// moments not due) in its second pass.  Dynamic LDS of K * 64 V floats per
+// due moment (and at least one such stage).
 template <int N, typename XT, typename GT, int V, int NTM>
 __global__ __launch_bounds__(64 * kWaveMaxK) __attribute__((amdgpu_waves_per_eu(8)))
 void k_sgdm_averaged_momenta_waves(StepParams p0, uint32_t mask, int32_t K) {
 #pragma clang fp contract(off)
-  const StepParams p = device_scalars(p0);
   constexpr bool NTL = (NTM & 1) != 0, NTS = (NTM & 2) != 0;
-  __shared__ float lds[kWaveMaxK][64 * V];
-  const int32_t m = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  XT* __restrict__ x = reinterpret_cast<XT*>(p.x);
-  const GT* __restrict__ g = reinterpret_cast<const GT*>(p.g);
+  constexpr int E = 64 * V;
+  extern __shared__ __align__(16) float stage[];
+  const int32_t m = __builtin_amdgcn_readfirstlane((int32_t)(threadIdx.x >> 6));
+  const int64_t e0 = group_piece(p0.group) * E, row = (int64_t)m * p0.P + e0;
+  const uint32_t o = (threadIdx.x & 63) * V;
+  const int32_t in_row = left_in_row(e0, p0.P), n = in_row - (int32_t)o;
+  XT* x = reinterpret_cast<XT*>(p0.x) + row;
+  const GT* g = reinterpret_cast<const GT*>(p0.g) + row;
   const double rk = 1.0 / (double)K;
-  const float sc = p.scale != nullptr ? load_uniform(p.scale + __builtin_amdgcn_readfirstlane(m)) : 1.0f;
 
-  // the mean over the replicas of val (this wave's row values), through
-  // LDS, written back into val
-  auto average = [&](float (&val)[V], bool in) {
-#pragma unroll
-    for (int t = 0; t < V; ++t) lds[m][t * 64 + lane] = val[t];
-    __syncthreads();
-    for (int t = m; in && t < V; t += K) {
-      const float s0 = lds[0][t * 64 + lane];
-      double d = 0.0;
-#pragma unroll 4
-      for (int32_t q = 1; q < K; ++q) mean_add(d, lds[q][t * 64 + lane], s0);
-      lds[0][t * 64 + lane] = mean_of(s0, d, rk);
-    }
-    __syncthreads();
-#pragma unroll
-    for (int t = 0; t < V; ++t) val[t] = lds[0][t * 64 + lane];
-    __syncthreads();
-  };
-
-  for (int64_t tile = blockIdx.x; tile < p.tiles; tile += gridDim.x) {
-    const int64_t e = tile * (int64_t)(64 * V) + (int64_t)lane * V;
-    const bool in = e < p.P;
-    const int64_t r = (int64_t)m * p.P + e;
+  auto piece = [&](auto full) {
+    constexpr bool F = decltype(full)::value;
     float gv[V], xv[V], uv[N][V];
+    load_n<F, GT, V, NTL>(g, o, n, gv);
 #pragma unroll
-    for (int t = 0; t < V; ++t) gv[t] = xv[t] = 0.0f;
-#pragma unroll
-    for (int j = 0; j < N; ++j)
-#pragma unroll
-      for (int t = 0; t < V; ++t) uv[j][t] = 0.0f;
-    if (in) {
-      load_v<GT, V, NTL>(g, r, gv);
-      load_v<XT, V, NTL>(x, r, xv);
-#pragma unroll
-      for (int j = 0; j < N; ++j) load_v<float, V, NTL>(p.u[j], r, uv[j]);
-    }
+    for (int j = 0; j < N; ++j) load_n<F, float, V, NTL>(p0.u[j] + row, o, n, uv[j]);
+    load_n<F, XT, V, NTL>(x, o, n, xv);
+    const float sc = p0.scale != nullptr ? load_uniform(p0.scale + m) : 1.0f;
+    const StepParams p = device_scalars(p0);
+    const OuterAhead<1> none{};
 #pragma unroll
     for (int t = 0; t < V; ++t) {
       const float gh = sc * gv[t];
 #pragma unroll
       for (int j = 0; j < N; ++j) uv[j][t] = __builtin_fmaf(p.beta[j], uv[j][t], p.omb[j] * gh);
     }
+    int32_t due = 0;
+#pragma unroll
+    for (int j = 0; j < N; ++j)
+      if ((mask >> (j + 1)) & 1u) lds_put<V>(stage + (due++ * K + m) * E + o, uv[j]);
+    __syncthreads();
+    average_stages<E>(stage, K, due, in_row, rk, p0.outer, false, none, e0);
+    __syncthreads();
+    due = 0;
 #pragma unroll
     for (int j = 0; j < N; ++j) {
-      if ((mask >> (j + 1)) & 1u) average(uv[j], in);
-      if (in) store_v<float, V, NTS>(p.u[j], r, uv[j]);
+      if ((mask >> (j + 1)) & 1u) lds_get<V>(stage + due++ * K * E + o, uv[j]);
+      store_n<F, float, V, NTS>(p0.u[j] + row, o, n, uv[j]);
     }
 #pragma unroll
     for (int t = 0; t < V; ++t) {
@@ -1058,30 +1247,38 @@ void k_sgdm_averaged_momenta_waves(StepParams p0, uint32_t mask, int32_t K) {
       for (int j = 0; j < N; ++j) delta = __builtin_fmaf(p.w[j], uv[j][t], delta);
       xv[t] = as_stored<XT>(__builtin_fmaf(-p.lr, delta, xv[t]));
     }
-    if (mask & 1u) average(xv, in);
-    if (in) store_v<XT, V, NTS>(x, r, xv);
-  }
+    if (mask & 1u) {
+      __syncthreads();  // every wave has read the moments' means
+      lds_put<V>(stage + m * E + o, xv);
+      __syncthreads();
+      average_stages<E>(stage, K, 1, in_row, rk, p0.outer, false, none, e0);
+      __syncthreads();
+      lds_get<V>(stage + o, xv);
+    }
+    store_n<F, XT, V, NTS>(x, o, n, xv);
+  };
+  if (in_row >= E) piece(BoolC<true>{});
+  else piece(BoolC<false>{});
 }
 
-// ADOPT's first update with the previous-v order: v = g^2, nothing else.
-template <typename GT, int V, int U, bool NT>
-__global__ __launch_bounds__(kBlock) void k_adopt_init_v(const void* gp, float* vp, int64_t P, int64_t tiles) {
-  const int64_t row = (int64_t)blockIdx.y * P;
-  const GT* __restrict__ g = reinterpret_cast<const GT*>(gp) + row;
-  float* __restrict__ v = vp + row;
-  for (int64_t tile = blockIdx.x; tile < tiles; tile += gridDim.x) {
-    const int64_t base = tile * (int64_t)(kBlock * V * U);
+// ADOPT's first update with the previous-v order: v = g^2, nothing else,
+// over the n = K P elements as flat arrays.
+template <typename GT, int V>
+__global__ __launch_bounds__(kBlock) void k_adopt_init_v(const void* gp, float* vp, int64_t total) {
+  const int64_t base = launch_tile() * (kBlock * V);
+  const uint32_t o = threadIdx.x * V;
+  const int32_t n = left_in_row(base, total) - (int32_t)o;
+  const GT* g = reinterpret_cast<const GT*>(gp) + base;
+  float a[V];
+  auto piece = [&](auto full) {
+    constexpr bool F = decltype(full)::value;
+    load_n<F, GT, V, false>(g, o, n, a);
 #pragma unroll
-    for (int k = 0; k < U; ++k) {
-      const int64_t e = base + ((int64_t)k * kBlock + threadIdx.x) * V;
-      if (e >= P) continue;
-      float a[V];
-      load_v<GT, V, NT>(g, e, a);
-#pragma unroll
-      for (int t = 0; t < V; ++t) a[t] = a[t] * a[t];
-      store_v<float, V, NT>(v, e, a);
-    }
-  }
+    for (int t = 0; t < V; ++t) a[t] = a[t] * a[t];
+    store_n<F, float, V, false>(vp + base, o, n, a);
+  };
+  if (n >= V) piece(BoolC<true>{});
+  else if (n > 0) piece(BoolC<false>{});
 }
 
 // --------------------------------------------------------- replica mean
@@ -1089,115 +1286,99 @@ __global__ __launch_bounds__(kBlock) void k_adopt_init_v(const void* gp, float* 
 struct MeanParams {
   void* state[kMaxMeanStates];  // [K][P] buffers of one storage type
   int64_t P;
-  int64_t tiles;
+  int64_t tiles;                // k_replica_mean_stats: workgroups
   int32_t K;
+  int32_t group;                // group_piece
   int32_t outer_state;          // index of x in state[] when OuterOpt applies, else -1
   OuterParams outer;
 };
 
-// E_m[S] for the state blockIdx.y: every element becomes
+// E_m[S] for the state blockIdx.z: every element becomes
 // S^0 + (sum_{m>=1} (S^m - S^0)) / K (mean_of) and is stored to all K rows.
 // Each thread reads the K rows of its own columns and writes them back, so
 // the in-place update has no cross-thread hazard.
-template <typename T, int V, bool NT, int U = 1, int C = 0>
+template <typename T, int V, bool NT>
 __global__ __launch_bounds__(kBlock) void k_replica_mean(MeanParams p) {
-  T* __restrict__ s = reinterpret_cast<T*>(p.state[blockIdx.y]);
+  T* s = reinterpret_cast<T*>(p.state[blockIdx.z]);
   const double rk = 1.0 / (double)p.K;
-  for (int64_t tile = blockIdx.x; tile < p.tiles; tile += gridDim.x) {
-    float s0[U][V];
-    double d[U][V];
+  // a wave's elements are one piece of the tile
+  const int64_t base = tile_elem<kBlock * V, 64 * V>(launch_tile(), 0);
+  const uint32_t o = (uint32_t)tile_elem<kBlock * V, 64 * V>(0, (int)threadIdx.x * V);
+  const int32_t n = left_in_row(base, p.P) - (int32_t)o, nw = __builtin_amdgcn_readfirstlane(n);
+  auto piece = [&](auto full) {
+    constexpr bool F = decltype(full)::value;
+    float s0[V], q[V];
+    double d[V];
+    load_n<F, T, V, NT>(s + base, o, n, s0);
 #pragma unroll
-    for (int k = 0; k < U; ++k) {
-      const int64_t e = tile_elem<kBlock * V * U, C>(tile, (k * kBlock + (int)threadIdx.x) * V);
-      if (e < p.P) load_v<T, V, NT>(s, e, s0[k]);
+    for (int t = 0; t < V; ++t) d[t] = 0.0;
+    // four rows' loads in flight
+    int32_t m = 1;
+    for (; m + 4 <= p.K; m += 4) {
+      float r[4][V];
 #pragma unroll
-      for (int t = 0; t < V; ++t) d[k][t] = 0.0;
+      for (int i = 0; i < 4; ++i) load_n<F, T, V, NT>(s + (int64_t)(m + i) * p.P + base, o, n, r[i]);
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int t = 0; t < V; ++t) mean_add(d[t], r[i][t], s0[t]);
     }
-#pragma unroll 4
-    for (int32_t m = 1; m < p.K; ++m) {
+    for (; m < p.K; ++m) {
+      load_n<F, T, V, NT>(s + (int64_t)m * p.P + base, o, n, q);
 #pragma unroll
-      for (int k = 0; k < U; ++k) {
-        const int64_t e = tile_elem<kBlock * V * U, C>(tile, (k * kBlock + (int)threadIdx.x) * V);
-        if (e >= p.P) continue;
-        float a[V];
-        load_v<T, V, NT>(s + (int64_t)m * p.P, e, a);
-#pragma unroll
-        for (int t = 0; t < V; ++t) mean_add(d[k][t], a[t], s0[k][t]);
-      }
+      for (int t = 0; t < V; ++t) mean_add(d[t], q[t], s0[t]);
     }
 #pragma unroll
-    for (int k = 0; k < U; ++k) {
-      const int64_t e = tile_elem<kBlock * V * U, C>(tile, (k * kBlock + (int)threadIdx.x) * V);
-      if (e >= p.P) continue;
-#pragma unroll
-      for (int t = 0; t < V; ++t) s0[k][t] = mean_of(s0[k][t], d[k][t], rk);
-      if ((int32_t)blockIdx.y == p.outer_state) outer_step<V>(p.outer, e, s0[k]);
-#pragma unroll 4
-      for (int32_t m = 0; m < p.K; ++m) store_v<T, V, NT>(s + (int64_t)m * p.P, e, s0[k]);
-    }
-  }
+    for (int t = 0; t < V; ++t) s0[t] = mean_of(s0[t], d[t], rk);
+    if ((int32_t)blockIdx.z == p.outer_state) outer_step_n<F, V>(p.outer, base + o, n, s0);
+    for (m = 0; m < p.K; ++m) store_n<F, T, V, NT>(s + (int64_t)m * p.P + base, o, n, s0);
+  };
+  if (nw >= 64 * V) piece(BoolC<true>{});
+  else if (nw > 0) piece(BoolC<false>{});
 }
 
 // The same mean with whole waves per replica row (blockDim = 64 K / R,
 // 1 < K <= kWaveMaxK, R | K; dynamic LDS of K * 64 * V floats): each
 // workgroup takes one piece of 64 V consecutive elements (a 1 KiB access
 // for fp32 and bf16 rows), wave w loads the pieces of rows w, w + W, ...,
-// w + (R - 1) W (W = K / R waves), the K pieces meet in LDS, column t of
-// the piece is averaged by wave t mod W with mean_add / mean_of in replica
-// order (so every element gets exactly the value k_replica_mean gives),
-// the OuterOpt runs element by element on x, and each wave stores the mean
-// to its rows.  Each wave then issues R loads and R stores per piece, as a
-// plain copy does; a thread that walks all K rows of its columns
-// (k_replica_mean) ran the K = 4 mean at 74% of the HBM peak on MI355X,
-// this kernel at 82.6%.  With K = 16 and one row per wave only two
-// 16-wave workgroups fit on a CU and every barrier idles 16 waves; two rows
-// per wave took the K = 16 mean from 8.2 to 7.6 ms (69% to 74.5%) and the
-// K = 8 bf16 mean from 0.745 to 0.685 ms, four rows per wave gave nothing.
-// Barriers are reached by every thread, also in the row tail.
+// w + (R - 1) W (W = K / R waves), the K pieces meet in LDS, all waves share
+// the means (mean_add / mean_of in replica order, so every element gets
+// exactly the value k_replica_mean gives), the OuterOpt runs element by
+// element on x, and each wave stores the mean to its rows.  Each wave then
+// issues R loads and R stores per piece, as a plain copy does; a thread that
+// walks all K rows of its columns (k_replica_mean) ran the K = 4 mean at 74%
+// of the HBM peak on MI355X, this kernel at 82.6%.
 template <typename T, int V, bool NT, int R = 1>
 __global__ __launch_bounds__(64 * kWaveMaxK / R) void k_replica_mean_waves(MeanParams p) {
-  extern __shared__ float lds_mean[];  // [K][64 V]
-  T* __restrict__ s = reinterpret_cast<T*>(p.state[blockIdx.y]);
-  const int32_t K = p.K, W = K / R, w = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const double rk = 1.0 / (double)K;
-  const bool outer = (int32_t)blockIdx.y == p.outer_state;
-  for (int64_t tile = blockIdx.x; tile < p.tiles; tile += gridDim.x) {
-    const int64_t e = tile * (int64_t)(64 * V) + (int64_t)lane * V;
-    const bool in = e < p.P;
+  constexpr int E = 64 * V, U = kPieceMaxU * V / 4;
+  extern __shared__ __align__(16) float stage[];
+  const int32_t K = p.K, W = K / R;
+  const int32_t w = __builtin_amdgcn_readfirstlane((int32_t)(threadIdx.x >> 6));
+  const int64_t e0 = group_piece(p.group) * E;
+  const uint32_t o = (threadIdx.x & 63) * V;
+  const int32_t in_row = left_in_row(e0, p.P), n = in_row - (int32_t)o;
+  T* s = reinterpret_cast<T*>(p.state[blockIdx.z]) + e0;
+  const bool outer = (int32_t)blockIdx.z == p.outer_state;
+
+  auto piece = [&](auto full) {
+    constexpr bool F = decltype(full)::value;
     float a[R][V];
 #pragma unroll
-    for (int r = 0; r < R; ++r)
+    for (int r = 0; r < R; ++r) load_n<F, T, V, NT>(s + (int64_t)(w + r * W) * p.P, o, n, a[r]);
+    OuterAhead<U> ahead;
+    if (outer) outer_ahead<E>(p.outer, e0, in_row, ahead);
 #pragma unroll
-      for (int t = 0; t < V; ++t) a[r][t] = 0.0f;
-    if (in) {
-#pragma unroll
-      for (int r = 0; r < R; ++r) load_v<T, V, NT>(s + (int64_t)(w + r * W) * p.P, e, a[r]);
-    }
-#pragma unroll
-    for (int r = 0; r < R; ++r)
-#pragma unroll
-      for (int t = 0; t < V; ++t) lds_mean[((w + r * W) * V + t) * 64 + lane] = a[r][t];
+    for (int r = 0; r < R; ++r) lds_put<V>(stage + (w + r * W) * E + o, a[r]);
     __syncthreads();
-    for (int t = w; in && t < V; t += W) {
-      const float s0 = lds_mean[t * 64 + lane];
-      double d = 0.0;
-      for (int32_t q = 1; q < K; ++q) mean_add(d, lds_mean[(q * V + t) * 64 + lane], s0);
-      lds_mean[t * 64 + lane] = mean_of(s0, d, rk);
-    }
+    average_stages<E>(stage, K, 1, in_row, 1.0 / (double)K, p.outer, outer, ahead, e0);
     __syncthreads();
-    if (outer) {
-      outer_step_piece<V>(p.outer, tile * (int64_t)(64 * V), p.P, W, w, lane, lds_mean);
-      __syncthreads();
-    }
-    if (in) {
-      float b[V];
+    float b[V];
+    lds_get<V>(stage + o, b);
 #pragma unroll
-      for (int t = 0; t < V; ++t) b[t] = lds_mean[t * 64 + lane];
-#pragma unroll
-      for (int r = 0; r < R; ++r) store_v<T, V, NT>(s + (int64_t)(w + r * W) * p.P, e, b);
-    }
-    __syncthreads();
-  }
+    for (int r = 0; r < R; ++r) store_n<F, T, V, NT>(s + (int64_t)(w + r * W) * p.P, o, n, b);
+  };
+  if (in_row >= E) piece(BoolC<true>{});
+  else piece(BoolC<false>{});
 }
 
 // ----------------------------------------------------- global-norm clip
@@ -1236,41 +1417,35 @@ __device__ __forceinline__ double wave_sum(double a) {
 }
 
 // Partial sums of g^2 in fp64 for replica blockIdx.y; each block writes
-// one partial (fixed order: deterministic for a fixed grid).
-template <typename GT, int V, int U, int C = 0>
-__global__ __launch_bounds__(kBlock) void k_sumsq_partial(const void* gp, int64_t P, int64_t tiles,
-                                                          double* __restrict__ partials) {
-  const int64_t row = (int64_t)blockIdx.y * P;
-  const GT* __restrict__ g = reinterpret_cast<const GT*>(gp) + row;
+// one partial (fixed order: deterministic for a fixed grid).  A tile that
+// lies in the row issues its U loads back to back, so U vector loads per
+// lane are in flight; the last ones are read element by element.
+template <typename GT, int V, int U, int C>
+__global__ __launch_bounds__(kBlock) void k_sumsq_partial(const void* gp, int64_t P, double* __restrict__ partials) {
+  constexpr int T = kBlock * V * U;
+  const int64_t base = tile_elem<T, C>(blockIdx.x, 0);
+  const GT* __restrict__ g = reinterpret_cast<const GT*>(gp) + (int64_t)blockIdx.y * P + base;
+  const int32_t in_row = left_in_row(base, P);
+  const uint32_t last = (uint32_t)tile_elem<T, C>(0, ((U - 1) * kBlock + (kBlock - 1)) * V) + V;
   double acc = 0.0;
-  for (int64_t tile = blockIdx.x; tile < tiles; tile += gridDim.x) {
+  auto tile = [&](auto full) {
+    constexpr bool F = decltype(full)::value;
     float a[U][V];
-    // The thread's last slot lies furthest along the row: when it is in
-    // range, all U loads are issued unconditionally, back to back, so U
-    // vector loads per lane are in flight (a guarded load per slot is
-    // waited on before the next is issued).
-    if (tile_elem<kBlock * V * U, C>(tile, ((U - 1) * kBlock + (int)threadIdx.x) * V) < P) {
-#pragma unroll
-      for (int k = 0; k < U; ++k)
-        load_v<GT, V, false>(g, tile_elem<kBlock * V * U, C>(tile, (k * kBlock + (int)threadIdx.x) * V), a[k]);
-    } else {
-#pragma unroll
-      for (int k = 0; k < U; ++k) {
-        const int64_t e = tile_elem<kBlock * V * U, C>(tile, (k * kBlock + (int)threadIdx.x) * V);
-        if (e < P) load_v<GT, V, false>(g, e, a[k]);
-      }
-    }
 #pragma unroll
     for (int k = 0; k < U; ++k) {
-      const int64_t e = tile_elem<kBlock * V * U, C>(tile, (k * kBlock + (int)threadIdx.x) * V);
-      if (e >= P) continue;
+      const uint32_t o = (uint32_t)tile_elem<T, C>(0, (k * kBlock + (int)threadIdx.x) * V);
+      load_n<F, GT, V, false>(g, o, in_row - (int32_t)o, a[k]);
+    }
+#pragma unroll
+    for (int k = 0; k < U; ++k)
 #pragma unroll
       for (int t = 0; t < V; ++t) {
-        const double d = (double)a[k][t];
+        const double d = (double)a[k][t];  // 0 beyond the row
         acc = __builtin_fma(d, d, acc);
       }
-    }
-  }
+  };
+  if (in_row >= (int32_t)last) tile(BoolC<true>{});
+  else tile(BoolC<false>{});
   acc = wave_sum(acc);
   __shared__ double ws[kBlock / 64];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -1334,93 +1509,101 @@ constexpr int kStatsStride = 4 + 2 * kStatsMaxK;  // doubles per state (layout i
 // averaging, the averaging diagnostics of state blockIdx.y: ||cbar||^2,
 // sum_m ||c^m - cbar||^2, ||xo||^2, ||c^m||^2 and <c^m, cbar>, with
 // c^m = S^m, or c^m = xo - x^m for x under a Nesterov OuterOpt.
-// blockDim = 64 K (1 <= K <= kStatsMaxK), dynamic LDS of K * 64 * V
-// floats.  Workgroup b takes q pieces of 64 V elements, pieces
-// ((b / 8) q + i) 8 + b mod 8 for i < q: each XCD keeps one piece in eight,
-// and as workgroups are dispatched in order the pieces in flight stay a
-// compact window, as in the plain mean (a fixed grid of workgroups
-// striding over the row scattered them and ran 30% slower).  Each wave
-// keeps fp64 sums for its own replica (wave 0 also those of cbar and xo):
-// a lane forms the V products of a piece in fp32 (one rounding each, about
-// 6e-8 relative) and adds their fp32 sum to the fp64 sums, which keeps the
-// fp64 work per element to a fraction of an operation.  The workgroup
-// writes its kStatsSums(K) sums, contiguous, to
+// blockDim = 64 K (1 <= K <= kStatsMaxK), dynamic LDS of 2 K * 64 V floats.
+// Workgroup b takes Q pieces of 64 V elements, pieces ((b / 8) Q + i) 8 +
+// b mod 8 for i < Q: each XCD keeps one piece in eight, and as workgroups
+// are dispatched in order the pieces in flight stay a compact window, as in
+// the plain mean (a fixed grid of workgroups striding over the row scattered
+// them and ran 30% slower).  The next piece's loads are issued before a
+// piece's exchange, and consecutive pieces use two LDS buffers in turn, so a
+// piece takes two barriers.  Each wave keeps fp64 sums for its own replica
+// (wave 0 also those of cbar and xo): a lane forms the V products of a piece
+// in fp32 (one rounding each, about 6e-8 relative) and adds their fp32 sum
+// to the fp64 sums, which keeps the fp64 work per element to a fraction of
+// an operation.  The workgroup writes its kStatsSums(K) sums, contiguous, to
 // partials[state][workgroup][sum]:
 //   0 ||cbar||^2, 1 sum_m ||c^m - cbar||^2, 2 ||xo||^2,
 //   3 + m ||c^m||^2, 3 + K + m <c^m, cbar>.
 __host__ __device__ constexpr int kStatsSums(int K) { return 3 + 2 * K; }
 
-template <typename T, int V>
-__global__ __launch_bounds__(64 * kStatsMaxK) void k_replica_mean_stats(MeanParams p, int32_t q,
-                                                                          double* __restrict__ partials) {
-  extern __shared__ float lds_stats[];  // [K][64 V]
+template <typename T, int V, int Q>
+__global__ __launch_bounds__(64 * kStatsMaxK) void k_replica_mean_stats(MeanParams p, double* __restrict__ partials) {
+  constexpr int E = 64 * V;
+  extern __shared__ __align__(16) float stage[];  // [2][K][64 V]
   __shared__ double red[kStatsMaxK][5];
-  T* __restrict__ s = reinterpret_cast<T*>(p.state[blockIdx.y]);
-  const int32_t K = p.K, m = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const bool outer = (int32_t)blockIdx.y == p.outer_state && p.outer.xo != nullptr;
+  const int32_t K = p.K, lane = threadIdx.x & 63;
+  const int32_t m = __builtin_amdgcn_readfirstlane((int32_t)(threadIdx.x >> 6));
+  const int64_t block = launch_tile();
+  if (block >= p.tiles) return;
+  const bool outer = (int32_t)blockIdx.z == p.outer_state && p.outer.xo != nullptr;
   const double rk = 1.0 / (double)K;
-  T* __restrict__ row = s + (int64_t)m * p.P;
+  T* row = reinterpret_cast<T*>(p.state[blockIdx.z]) + (int64_t)m * p.P;
+  const uint32_t o = lane * V;
   double a_sq = 0.0, a_dot = 0.0, a_var = 0.0, a_mean = 0.0, a_ref = 0.0;
-  for (int32_t i = 0; i < q; ++i) {
-    const int64_t tile = ((int64_t)(blockIdx.x >> 3) * q + i) * 8 + (blockIdx.x & 7);
-    if (tile >= p.tiles) break;  // uniform over the workgroup
-    const int64_t e = tile * (int64_t)(64 * V) + (int64_t)lane * V;
-    const bool in = e < p.P;
-    float a[V], xo[V];
-#pragma unroll
-    for (int t = 0; t < V; ++t) a[t] = xo[t] = 0.0f;
-    if (in) {
-      load_v<T, V, true>(row, e, a);
-      if (outer) load_v<float, V, false>(p.outer.xo, e, xo);
+  float a[V], nx[V] = {};
+  auto first = [&](int i) { return (((block >> 3) * Q + i) * 8 + (block & 7)) * E; };
+  auto fetch = [&](int64_t e0, float (&to)[V]) {
+    const int32_t in_row = left_in_row(e0, p.P), n = in_row - (int32_t)o;
+    if (in_row >= E) load_n<true, T, V, true>(row + e0, o, n, to);
+    else load_n<false, T, V, true>(row + e0, o, n, to);
+  };
+  fetch(first(0), a);
+  for (int i = 0; i < Q; ++i) {
+    const int64_t e0 = first(i);
+    if (e0 >= p.P) break;  // uniform over the workgroup
+    const int32_t in_row = left_in_row(e0, p.P), n = in_row - (int32_t)o;
+    float* buf = stage + (i & 1) * K * E;
+    if (i + 1 < Q) fetch(first(i + 1), nx);
+    float xo[V];
+    if (outer) {
+      if (in_row >= E) load_n<true, float, V, false>(p.outer.xo + e0, o, n, xo);
+      else load_n<false, float, V, false>(p.outer.xo + e0, o, n, xo);
     }
-#pragma unroll
-    for (int t = 0; t < V; ++t) lds_stats[(m * V + t) * 64 + lane] = a[t];
+    lds_put<V>(buf + m * E + o, a);
     __syncthreads();
-    for (int t = m; in && t < V; t += K) {
-      const float s0 = lds_stats[t * 64 + lane];
-      double d = 0.0;
-      for (int32_t q = 1; q < K; ++q) mean_add(d, lds_stats[(q * V + t) * 64 + lane], s0);
-      lds_stats[t * 64 + lane] = mean_of(s0, d, rk);
-    }
+    average_stages<E>(buf, K, 1, in_row, rk, p.outer, false, OuterAhead<1>{}, e0);
     __syncthreads();
-    float mean[V];
-#pragma unroll
-    for (int t = 0; t < V; ++t) mean[t] = lds_stats[t * 64 + lane];
+    float mean[V], out[V];
+    lds_get<V>(buf + o, mean);
     if (outer) {
       __syncthreads();  // every wave has read the means before the outer step rewrites them
-      outer_step_piece<V>(p.outer, tile * (int64_t)(64 * V), p.P, K, m, lane, lds_stats);
+      if (p.outer.update)
+        for (int32_t j = threadIdx.x; j < E; j += blockDim.x)
+          if (j < in_row) buf[j] = outer_element(p.outer, e0 + j, p.outer.xo[e0 + j], p.outer.mom[e0 + j], buf[j]);
       __syncthreads();
+      lds_get<V>(buf + o, out);
+    } else {
+#pragma unroll
+      for (int t = 0; t < V; ++t) out[t] = mean[t];
     }
     // store first, then reduce the diagnostics while the stores drain
-    if (in) {
-      float out[V];
+    if (in_row >= E) store_n<true, T, V, true>(row + e0, o, n, out);
+    else store_n<false, T, V, true>(row + e0, o, n, out);
+    // the piece's V terms in fp32, added to the fp64 sums once per piece
+    // (values, means and outer parameters beyond the row are 0)
+    float f_sq = 0.0f, f_dot = 0.0f, f_var = 0.0f, f_mean = 0.0f, f_ref = 0.0f;
 #pragma unroll
-      for (int t = 0; t < V; ++t) out[t] = outer ? lds_stats[t * 64 + lane] : mean[t];
-      store_v<T, V, true>(row, e, out);
-      // the piece's V terms in fp32, added to the fp64 sums once per piece
-      float f_sq = 0.0f, f_dot = 0.0f, f_var = 0.0f, f_mean = 0.0f, f_ref = 0.0f;
-#pragma unroll
-      for (int t = 0; t < V; ++t) {
-        const float cbar = outer ? xo[t] - mean[t] : mean[t];
-        const float c = outer ? xo[t] - a[t] : a[t];
-        const float dv = a[t] - mean[t];  // c - cbar up to sign
-        f_sq = __builtin_fmaf(c, c, f_sq);
-        f_dot = __builtin_fmaf(c, cbar, f_dot);
-        f_var = __builtin_fmaf(dv, dv, f_var);
-        if (m == 0) {
-          f_mean = __builtin_fmaf(cbar, cbar, f_mean);
-          if (outer) f_ref = __builtin_fmaf(xo[t], xo[t], f_ref);
-        }
-      }
-      a_sq += (double)f_sq;
-      a_dot += (double)f_dot;
-      a_var += (double)f_var;
+    for (int t = 0; t < V; ++t) {
+      const float cbar = outer ? xo[t] - mean[t] : mean[t];
+      const float c = outer ? xo[t] - a[t] : a[t];
+      const float dv = a[t] - mean[t];  // c - cbar up to sign
+      f_sq = __builtin_fmaf(c, c, f_sq);
+      f_dot = __builtin_fmaf(c, cbar, f_dot);
+      f_var = __builtin_fmaf(dv, dv, f_var);
       if (m == 0) {
-        a_mean += (double)f_mean;
-        if (outer) a_ref += (double)f_ref;
+        f_mean = __builtin_fmaf(cbar, cbar, f_mean);
+        if (outer) f_ref = __builtin_fmaf(xo[t], xo[t], f_ref);
       }
     }
-    __syncthreads();
+    a_sq += (double)f_sq;
+    a_dot += (double)f_dot;
+    a_var += (double)f_var;
+    if (m == 0) {
+      a_mean += (double)f_mean;
+      if (outer) a_ref += (double)f_ref;
+    }
+#pragma unroll
+    for (int t = 0; t < V; ++t) a[t] = nx[t];
   }
   // the workgroup's sums, fixed order
   const double sq = wave_sum(a_sq), dot = wave_sum(a_dot), var = wave_sum(a_var);
@@ -1442,70 +1625,68 @@ __global__ __launch_bounds__(64 * kStatsMaxK) void k_replica_mean_stats(MeanPara
     else if (k == 2) v = red[0][4];
     else if (k < 3 + K) v = red[k - 3][0];
     else v = red[k - 3 - K][1];
-    partials[((int64_t)blockIdx.y * gridDim.x + blockIdx.x) * ns + k] = v;
+    partials[((int64_t)blockIdx.z * p.tiles + block) * ns + k] = v;
   }
 }
 
-// Fixed-order reduction of the workgroup sums, in two levels.  Each thread
-// adds whole rows of kStatsSums(K) sums (contiguous in memory) in row
-// order, keeping every sum in its own fp64 register, then the block adds
-// the threads' totals wave by wave in order.
-constexpr int kStatsChunk = 8192;
+// Fixed-order reduction of the workgroup sums, in two levels: rows of
+// ns = kStatsSums(K) sums, contiguous in memory.  Thread t adds sum t mod ns
+// of rows t / ns, t / ns + G, ... (G rows per pass, so consecutive threads
+// read consecutive sums), four rows in flight, and the G group totals are
+// added in order.  (A thread that added whole rows waited for each of its ns
+// loads in turn, and one workgroup per 8192 rows left most CUs idle.)
 constexpr int kStatsMaxSums = 3 + 2 * kStatsMaxK;
+constexpr int kStatsChunk = 256;    // rows of a first-level workgroup
+constexpr int kStatsBlock = 512;
 
-__device__ __forceinline__ void stats_block_sum(double (&acc)[kStatsMaxSums], int ns, double* __restrict__ dst) {
-  __shared__ double red[4][kStatsMaxSums];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-#pragma unroll
-  for (int k = 0; k < kStatsMaxSums; ++k) {
-    if (k < ns) {
-      const double w = wave_sum(acc[k]);
-      if (lane == 0) red[wave][k] = w;
+// Sum k of rows [lo, hi) of q (row r at q + r * stride) into tot[k], k < ns.
+__device__ __forceinline__ void stats_sum_rows(const double* __restrict__ q, int64_t stride, int64_t lo, int64_t hi,
+                                               int32_t ns, double* tot) {
+  __shared__ double part[kStatsBlock];
+  const int32_t G = kStatsBlock / ns, k = threadIdx.x % ns, first = threadIdx.x / ns;
+  if (first < G) {
+    double a0 = 0.0, a1 = 0.0, a2 = 0.0, a3 = 0.0;
+    int64_t r = lo + first;
+    for (; r + 3 * G < hi; r += 4 * G) {
+      const double b0 = q[r * stride + k], b1 = q[(r + G) * stride + k];
+      const double b2 = q[(r + 2 * G) * stride + k], b3 = q[(r + 3 * G) * stride + k];
+      a0 += b0;
+      a1 += b1;
+      a2 += b2;
+      a3 += b3;
     }
+    for (; r < hi; r += G) a0 += q[r * stride + k];
+    part[threadIdx.x] = (a0 + a1) + (a2 + a3);
   }
   __syncthreads();
   if ((int)threadIdx.x < ns) {
-    const int k = threadIdx.x;
-    dst[k] = (red[0][k] + red[1][k]) + (red[2][k] + red[3][k]);
+    double t = 0.0;
+    for (int32_t i = 0; i < G; ++i) t += part[i * ns + threadIdx.x];
+    tot[threadIdx.x] = t;
   }
+  __syncthreads();
 }
 
-// Level 1: chunk blockIdx.x (kStatsChunk consecutive workgroup rows) of
-// state blockIdx.y into level1[state][chunk][sum].
-__global__ __launch_bounds__(256) void k_stats_reduce(const double* __restrict__ partials, int64_t nb, int32_t ns,
-                                                     double* __restrict__ level1) {
-  double acc[kStatsMaxSums];
-#pragma unroll
-  for (int k = 0; k < kStatsMaxSums; ++k) acc[k] = 0.0;
-  const double* __restrict__ q = partials + (int64_t)blockIdx.y * nb * ns;
+// Level 1: the sums of chunk blockIdx.x (kStatsChunk workgroup rows) of
+// state blockIdx.y replace the chunk's first row.
+__global__ __launch_bounds__(kStatsBlock) void k_stats_reduce(double* __restrict__ partials, int64_t nb, int32_t ns) {
+  __shared__ double tot[kStatsMaxSums];
+  double* q = partials + (int64_t)blockIdx.y * nb * ns;
   const int64_t lo = (int64_t)blockIdx.x * kStatsChunk;
   const int64_t hi = lo + kStatsChunk < nb ? lo + kStatsChunk : nb;
-  for (int64_t b = lo + threadIdx.x; b < hi; b += 256) {
-#pragma unroll
-    for (int k = 0; k < kStatsMaxSums; ++k)
-      if (k < ns) acc[k] += q[b * ns + k];
-  }
-  stats_block_sum(acc, ns, level1 + ((int64_t)blockIdx.y * gridDim.x + blockIdx.x) * ns);
+  stats_sum_rows(q, ns, lo, hi, ns, tot);
+  if ((int)threadIdx.x < ns) q[lo * ns + threadIdx.x] = tot[threadIdx.x];
 }
 
-// Level 2: the nc chunk rows of state blockIdx.x, in chunk order, into out
-// in the layout of mtdao.h (kStatsStride doubles per state; slot 3 and the
-// slots of workers m >= K are 0); the variance sum is divided by K.
-__global__ __launch_bounds__(256) void k_stats_finalize(const double* __restrict__ level1, int32_t nc, int32_t K,
-                                                       double* __restrict__ out) {
+// Level 2: the chunk sums of state blockIdx.x into out in the layout of
+// mtdao.h (kStatsStride doubles per state; slot 3 and the slots of workers
+// m >= K are 0); the variance sum is divided by K.
+__global__ __launch_bounds__(kStatsBlock) void k_stats_finalize(const double* __restrict__ partials, int64_t nb,
+                                                                int32_t K, double* __restrict__ out) {
   __shared__ double tot[kStatsMaxSums];
   const int32_t state = blockIdx.x, ns = kStatsSums(K);
-  double acc[kStatsMaxSums];
-#pragma unroll
-  for (int k = 0; k < kStatsMaxSums; ++k) acc[k] = 0.0;
-  const double* __restrict__ q = level1 + (int64_t)state * nc * ns;
-  for (int32_t c = threadIdx.x; c < nc; c += 256) {
-#pragma unroll
-    for (int k = 0; k < kStatsMaxSums; ++k)
-      if (k < ns) acc[k] += q[(int64_t)c * ns + k];
-  }
-  stats_block_sum(acc, ns, tot);
-  __syncthreads();
+  stats_sum_rows(partials + (int64_t)state * nb * ns, (int64_t)kStatsChunk * ns, 0,
+                 (nb + kStatsChunk - 1) / kStatsChunk, ns, tot);
   if (threadIdx.x < kStatsStride) {
     const int k = threadIdx.x;
     double t = 0.0;

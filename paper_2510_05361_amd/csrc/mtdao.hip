@@ -93,11 +93,10 @@ bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) ==
 int64_t esize(int32_t dt) { return dt == MTDAO_BF16 ? 2 : 4; }
 bool has_v(const mtdao_config& c) { return c.form != MTDAO_SGDM; }
 
-// Vector width of a row: 16-byte slots when every row start stays aligned.
-int vec_width(int32_t dtype_small, int64_t P) {
-  const int v = dtype_small == MTDAO_BF16 ? 8 : 4;
-  return (P % v == 0) ? v : 1;
-}
+// Elements of a 16-byte slot.  Every row length takes vector slots: rows
+// start at any element, and the kernels read the last partial slot of a row
+// element by element.
+constexpr int slot(int32_t dtype) { return dtype == MTDAO_BF16 ? 8 : 4; }
 
 int32_t validate(const mtdao_config* c, std::string* e) {
   if (!c) return fail(e, MTDAO_ERR_INVALID_ARG, "config is NULL");
@@ -188,9 +187,7 @@ uint32_t valid_bits(const mtdao_config& c) {
 // flight at once: 16 concurrent read streams at K = 16.)  One fp64 partial
 // per workgroup; P <= 2^40 keeps the count below 2^31.
 int32_t norm_blocks_for(int64_t P) {
-  const int V = (P % 4 == 0) ? 4 : 1;
-  const int64_t nb = V == 4 ? tiles_for<kBlock * 4 * kNormU, piece_for(4)>(P)
-                            : tiles_for<kBlock * kNormU, piece_for(1)>(P);
+  const int64_t nb = tiles_for<kBlock * 4 * kNormU, piece_for(4)>(P);
   return (int32_t)(nb < 1 ? 1 : nb);
 }
 
@@ -211,11 +208,6 @@ int32_t hip_check(std::string* e, hipError_t r, const char* what) {
   return MTDAO_OK;
 }
 
-dim3 grid_for(int64_t tiles, int32_t ny) {
-  const int64_t maxx = INT64_C(0x7fffffff);
-  return dim3((unsigned)(tiles < maxx ? (tiles > 0 ? tiles : 1) : maxx), (unsigned)ny, 1);
-}
-
 // ---------------------------------------------------------------- dispatch
 
 template <int V>
@@ -225,21 +217,15 @@ struct TypeC {
   using type = T;
 };
 
-// Calls f(form, n, xtype, gtype, vwidth) with compile-time constants for the
-// configuration of c and the runtime vector width V (4, or 1 when a row
-// length breaks the 4-element alignment of row starts).
+// Calls f(form, n, xtype, gtype) with compile-time constants for the
+// configuration of c.
 template <typename F>
-void dispatch_step(const mtdao_config& c, int V, F&& f) {
+void dispatch_step(const mtdao_config& c, F&& f) {
   auto with_types = [&](auto form, auto n) {
-    auto with_v = [&](auto xt, auto gt) {
-      // 4-element slots: 16-byte fp32 and 8-byte bf16 accesses per lane
-      if (V == 1) f(form, n, xt, gt, IntC<1>{});
-      else f(form, n, xt, gt, IntC<4>{});
-    };
-    if (c.param_dtype == MTDAO_F32 && c.grad_dtype == MTDAO_F32) with_v(TypeC<float>{}, TypeC<float>{});
-    else if (c.param_dtype == MTDAO_F32) with_v(TypeC<float>{}, TypeC<uint16_t>{});
-    else if (c.grad_dtype == MTDAO_F32) with_v(TypeC<uint16_t>{}, TypeC<float>{});
-    else with_v(TypeC<uint16_t>{}, TypeC<uint16_t>{});
+    if (c.param_dtype == MTDAO_F32 && c.grad_dtype == MTDAO_F32) f(form, n, TypeC<float>{}, TypeC<float>{});
+    else if (c.param_dtype == MTDAO_F32) f(form, n, TypeC<float>{}, TypeC<uint16_t>{});
+    else if (c.grad_dtype == MTDAO_F32) f(form, n, TypeC<uint16_t>{}, TypeC<float>{});
+    else f(form, n, TypeC<uint16_t>{}, TypeC<uint16_t>{});
   };
   auto with_form = [&](auto form) {
     switch (c.n_moments) {
@@ -254,177 +240,161 @@ void dispatch_step(const mtdao_config& c, int V, F&& f) {
   else with_form(IntC<kSgdm>{});
 }
 
+// 4-element slots: 16-byte fp32 and 8-byte bf16 accesses per lane.
+constexpr int kStepV = 4;
+
+// LDS of a wave-per-replica step: `stages` of K pieces of 64 kStepV floats,
+// and enough that a CU holds wave_resident(K) workgroups.
+size_t wave_lds(int stages, int K, int bytes, int64_t P) {
+  const size_t need = (size_t)stages * K * 64 * kStepV * sizeof(float);
+  return P * K * bytes >= kResidentMin ? std::max(need, resident_lds(wave_resident(K))) : need;
+}
+
 // The local step alone, over the K P elements of every buffer as flat
 // arrays.  Four elements per thread for every length: rows whose length is
 // no multiple of four used one element per thread before, and the step of
 // 16.8M + 37 bf16 parameters x 8 replicas took 1567 us so, 630 us now.
 void launch_step(const mtdao_config& c, StepParams p, hipStream_t st) {
-  dispatch_step(c, 4, [&](auto form, auto n, auto xt, auto gt, auto vw) {
-    constexpr int FORM = decltype(form)::value, N = decltype(n)::value, VV = decltype(vw)::value;
+  dispatch_step(c, [&](auto form, auto n, auto xt, auto gt) {
+    constexpr int FORM = decltype(form)::value, N = decltype(n)::value, V = kStepV;
     using XT = typename decltype(xt)::type;
     using GT = typename decltype(gt)::type;
-    if constexpr (VV == 4) {
-      constexpr StepLaunch L = step_launch((int)(sizeof(GT) + sizeof(XT)) + 4 * N + (FORM != kSgdm ? 4 : 0));
-      constexpr int B = L.threads;
-      constexpr int C = piece_for(VV), T = B * VV;
-      p.n = p.P * c.replicas;
-      p.rp = 1.0 / (double)p.P;
-      p.tiles = tiles_for<T, C>(p.n);
-      const dim3 grid = tile_grid(p.tiles);
-      const size_t lds = p.n * L.bytes >= kResidentMin ? resident_lds(L.resident) : 0;
-      if constexpr (FORM == kAdopt) {
-        if (c.adopt_order == MTDAO_ADOPT_CUR)
-          hipLaunchKernelGGL((k_local_step<FORM, N, XT, GT, VV, kStepNT, kCur, kNoScale, B>), grid, dim3(B), lds, st, p);
-        else
-          hipLaunchKernelGGL((k_local_step<FORM, N, XT, GT, VV, kStepNT, kPrev, kNoScale, B>), grid, dim3(B), lds, st,
-                             p);
-      } else if (p.scale == nullptr) {
-        hipLaunchKernelGGL((k_local_step<FORM, N, XT, GT, VV, kStepNT, kPrev, kNoScale, B>), grid, dim3(B), lds, st, p);
-      } else if (p.P >= C) {
-        hipLaunchKernelGGL((k_local_step<FORM, N, XT, GT, VV, kStepNT, kPrev, kTwoRows, B>), grid, dim3(B), lds, st, p);
-      } else {
-        hipLaunchKernelGGL((k_local_step<FORM, N, XT, GT, VV, kStepNT, kPrev, kAnyRows, B>), grid, dim3(B), lds, st, p);
-      }
+    constexpr StepLaunch L = step_launch((int)(sizeof(GT) + sizeof(XT)) + 4 * N + (FORM != kSgdm ? 4 : 0));
+    constexpr int B = L.threads;
+    p.n = p.P * c.replicas;
+    p.rp = 1.0 / (double)p.P;
+    const dim3 grid = tile_grid(tiles_for<B * V, piece_for(V)>(p.n));
+    const size_t lds = p.n * L.bytes >= kResidentMin ? resident_lds(L.resident) : 0;
+    auto go = [&](auto kernel) { hipLaunchKernelGGL(kernel, grid, dim3(B), lds, st, p); };
+    if constexpr (FORM == kAdopt) {
+      if (c.adopt_order == MTDAO_ADOPT_CUR) go(k_local_step<FORM, N, XT, GT, V, kStepNT, kCur, kNoScale, B>);
+      else go(k_local_step<FORM, N, XT, GT, V, kStepNT, kPrev, kNoScale, B>);
+    } else {
+      if (p.scale == nullptr) go(k_local_step<FORM, N, XT, GT, V, kStepNT, kPrev, kNoScale, B>);
+      else if (p.P >= 64 * V) go(k_local_step<FORM, N, XT, GT, V, kStepNT, kPrev, kTwoRows, B>);
+      else go(k_local_step<FORM, N, XT, GT, V, kStepNT, kPrev, kAnyRows, B>);
     }
   });
 }
 
-// The local step with the replica mean of the states in mask: grid over
-// tiles of one row, each thread covering all K replicas of its columns.
-void launch_step_sync(const mtdao_config& c, StepParams p, int V, uint32_t mask, hipStream_t st) {
-  dispatch_step(c, V, [&](auto form, auto n, auto xt, auto gt, auto vw) {
-    constexpr int FORM = decltype(form)::value, N = decltype(n)::value, VV = decltype(vw)::value;
+// The local step with the replica mean of the states in mask: one wavefront
+// per replica up to kWaveMaxK of them, else one thread per column.
+void launch_step_sync(const mtdao_config& c, StepParams p, uint32_t mask, hipStream_t st) {
+  dispatch_step(c, [&](auto form, auto n, auto xt, auto gt) {
+    constexpr int FORM = decltype(form)::value, N = decltype(n)::value, V = kStepV;
     using XT = typename decltype(xt)::type;
     using GT = typename decltype(gt)::type;
-    if (c.replicas > 1 && c.replicas <= kWaveMaxK) {
-      // one wavefront per replica
-      const int64_t per = (int64_t)64 * VV;
-      p.tiles = (p.P + per - 1) / per;
-      const dim3 grid = grid_for(p.tiles, 1), block(64 * c.replicas);
+    constexpr int kLoad = (int)(sizeof(GT) + sizeof(XT)) + 4 * N + (FORM != kSgdm ? 4 : 0);
+    const int K = c.replicas;
+    if (K > 1 && K <= kWaveMaxK) {
+      const int64_t pieces = (p.P + 64 * V - 1) / (64 * V);
+      const dim3 block(64 * K);
+      if (K > 8 && p.P % V == 0) {
+        auto go = [&](auto kernel) { hipLaunchKernelGGL(kernel, tile_grid(pieces), block, 0, st, p, mask, K); };
+        if constexpr (FORM == kAdopt) {
+          if (c.adopt_order == MTDAO_ADOPT_CUR) {
+            go(k_local_step_sync_waves_rounds<FORM, N, XT, GT, V, kStepNT, kCur>);
+            return;
+          }
+        }
+        go(k_local_step_sync_waves_rounds<FORM, N, XT, GT, V, kStepNT, kPrev>);
+        return;
+      }
+      p.group = row_group(p.P);
+      const dim3 grid = group_grid(pieces, p.group);
+      const size_t lds = wave_lds(__builtin_popcount(mask), K, kLoad, p.P);
+      auto go = [&](auto kernel) { hipLaunchKernelGGL(kernel, grid, block, lds, st, p, mask, K); };
       if constexpr (FORM == kAdopt) {
         if (c.adopt_order == MTDAO_ADOPT_CUR) {
-          hipLaunchKernelGGL((k_local_step_sync_waves<FORM, N, XT, GT, VV, kStepNT, kCur>), grid, block, 0, st, p, mask,
-                             c.replicas);
+          go(k_local_step_sync_waves<FORM, N, XT, GT, V, kStepNT, kCur>);
           return;
         }
       }
-      hipLaunchKernelGGL((k_local_step_sync_waves<FORM, N, XT, GT, VV, kStepNT, kPrev>), grid, block, 0, st, p, mask,
-                         c.replicas);
+      go(k_local_step_sync_waves<FORM, N, XT, GT, V, kStepNT, kPrev>);
       return;
     }
-    constexpr int C = piece_for(VV);
-    p.tiles = tiles_for<kBlock * VV, C>(p.P);
-    const dim3 grid = grid_for(p.tiles, 1);
+    const dim3 grid = tile_grid(tiles_for<kBlock * V, piece_for(V)>(p.P));
+    auto go = [&](auto kernel) { hipLaunchKernelGGL(kernel, grid, dim3(kBlock), 0, st, p, mask, K); };
     if constexpr (FORM == kAdopt) {
       if (c.adopt_order == MTDAO_ADOPT_CUR) {
-        hipLaunchKernelGGL((k_local_step_sync<FORM, N, XT, GT, VV, kStepNT, kCur, C>), grid, dim3(kBlock), 0, st, p,
-                           mask, c.replicas);
+        go(k_local_step_sync<FORM, N, XT, GT, V, kStepNT, kCur>);
         return;
       }
     }
-    hipLaunchKernelGGL((k_local_step_sync<FORM, N, XT, GT, VV, kStepNT, kPrev, C>), grid, dim3(kBlock), 0, st, p,
-                       mask, c.replicas);
+    go(k_local_step_sync<FORM, N, XT, GT, V, kStepNT, kPrev>);
   });
 }
 
 template <typename GT>
-void launch_adopt_init(const void* g, float* v, int64_t P, int32_t K, int V, hipStream_t st) {
-  const int64_t per = (int64_t)kBlock * 2;
-  if (V == 1) {
-    hipLaunchKernelGGL((k_adopt_init_v<GT, 1, 2, false>), grid_for((P + per - 1) / per, K), dim3(kBlock), 0, st,
-                       g, v, P, (P + per - 1) / per);
-  } else {
-    hipLaunchKernelGGL((k_adopt_init_v<GT, 4, 2, false>), grid_for((P + 4 * per - 1) / (4 * per), K), dim3(kBlock),
-                       0, st, g, v, P, (P + 4 * per - 1) / (4 * per));
-  }
+void launch_adopt_init(const void* g, float* v, int64_t n, hipStream_t st) {
+  hipLaunchKernelGGL((k_adopt_init_v<GT, 4>), tile_grid((n + 4 * kBlock - 1) / (4 * kBlock)), dim3(kBlock), 0, st, g, v,
+                     n);
 }
 
 template <typename GT>
-void launch_norm(const void* g, int64_t P, int32_t K, int V, int32_t nb, double* partials, hipStream_t st) {
-  if (V == 1) {
-    constexpr int C = piece_for(1);
-    hipLaunchKernelGGL((k_sumsq_partial<GT, 1, kNormU, C>), dim3(nb, K), dim3(kBlock), 0, st, g, P,
-                       tiles_for<kBlock * kNormU, C>(P), partials);
-  } else {
-    constexpr int C = piece_for(4);
-    hipLaunchKernelGGL((k_sumsq_partial<GT, 4, kNormU, C>), dim3(nb, K), dim3(kBlock), 0, st, g, P,
-                       tiles_for<kBlock * 4 * kNormU, C>(P), partials);
-  }
+void launch_norm(const void* g, int64_t P, int32_t K, int32_t nb, double* partials, hipStream_t st) {
+  // four workgroups (128 KiB of loads) per CU: K = 16, 60M, with the step it
+  // serves 3536 -> 3504 us
+  const size_t lds = P * K * (int64_t)sizeof(GT) >= kResidentMin ? resident_lds(4) : 0;
+  hipLaunchKernelGGL((k_sumsq_partial<GT, 4, kNormU, piece_for(4)>), dim3(nb, K), dim3(kBlock), lds, st, g, P, partials);
 }
 
 template <typename T>
-void launch_mean(MeanParams p, int nstates, int V, hipStream_t st) {
-  constexpr int VW = sizeof(T) == 2 ? 8 : 4;  // elements of a 16-byte slot
+void launch_mean(MeanParams p, int nstates, hipStream_t st) {
+  constexpr int V = sizeof(T) == 2 ? 8 : 4;  // elements of a 16-byte slot
   if (p.K > 1 && p.K <= kWaveMaxK) {
     // one piece of 64 V elements per workgroup; one wavefront per replica,
     // or per two replicas for even K > 8 and for bf16 rows at K = 8
     // (measured on MI355X at K = 8: bf16 x 72% of peak with two rows per
     // wave against 68% with one, fp32 states 75.7% against 77.2%)
-    const int vw = V == 1 ? 1 : VW;
-    p.tiles = (p.P + 64 * vw - 1) / (64 * vw);
     const bool two = p.K % 2 == 0 && (p.K > 8 || (p.K == 8 && sizeof(T) == 2));
-    const dim3 grid = grid_for(p.tiles, nstates), block(64 * (two ? p.K / 2 : p.K));
-    const size_t lds = (size_t)p.K * 64 * vw * sizeof(float);
-    if (two) {
-      if (vw == 1) hipLaunchKernelGGL((k_replica_mean_waves<T, 1, kMeanNT, 2>), grid, block, lds, st, p);
-      else hipLaunchKernelGGL((k_replica_mean_waves<T, VW, kMeanNT, 2>), grid, block, lds, st, p);
-    } else {
-      if (vw == 1) hipLaunchKernelGGL((k_replica_mean_waves<T, 1, kMeanNT>), grid, block, lds, st, p);
-      else hipLaunchKernelGGL((k_replica_mean_waves<T, VW, kMeanNT>), grid, block, lds, st, p);
-    }
+    p.group = row_group(p.P);
+    const dim3 grid = group_grid((p.P + 64 * V - 1) / (64 * V), p.group, nstates);
+    const dim3 block(64 * (two ? p.K / 2 : p.K));
+    const size_t lds = (size_t)p.K * 64 * V * sizeof(float);
+    if (two) hipLaunchKernelGGL((k_replica_mean_waves<T, V, kMeanNT, 2>), grid, block, lds, st, p);
+    else hipLaunchKernelGGL((k_replica_mean_waves<T, V, kMeanNT>), grid, block, lds, st, p);
     return;
   }
   // K = 1 (an outer step only) and K > kWaveMaxK: one thread per column
-  if (V == 1) {
-    p.tiles = tiles_for<kBlock, piece_for(1)>(p.P);
-    hipLaunchKernelGGL((k_replica_mean<T, 1, kMeanNT, 1, piece_for(1)>), grid_for(p.tiles, nstates), dim3(kBlock), 0,
-                       st, p);
-  } else {
-    p.tiles = tiles_for<VW * kBlock, piece_for(VW)>(p.P);
-    hipLaunchKernelGGL((k_replica_mean<T, VW, kMeanNT, 1, piece_for(VW)>), grid_for(p.tiles, nstates), dim3(kBlock),
-                       0, st, p);
-  }
+  hipLaunchKernelGGL((k_replica_mean<T, V, kMeanNT>), tile_grid(tiles_for<V * kBlock, piece_for(V)>(p.P), nstates),
+                     dim3(kBlock), 0, st, p);
 }
 
 // The diagnostics pass of nstates states of one storage type: V elements
-// per lane (16-byte accesses, or 1 when a row length breaks alignment), K
-// waves per workgroup, kStatsPieces pieces per workgroup, then the two
-// fixed-order reduction levels into out.  partials holds
-// nstates * kStatsSums(K) * (workgroups + chunks) doubles.
+// per lane (16-byte accesses), K waves per workgroup, kStatsPieces pieces
+// per workgroup, then the two fixed-order reduction levels into out.
+// partials holds nstates * kStatsSums(K) * workgroups doubles.
 //
 // Pieces per workgroup, measured on MI355X at 1.31B params x 4 replicas
 // (one state, DPP wave sums): 2 -> 7.65 ms, 3 -> 7.3 ms, 4 -> 6.9 ms,
 // 6 -> 7.35 ms, 8 -> 7.3 ms.  With shuffle-based wave sums the closing
 // reduction of each workgroup dominated below 4 (1 -> 14.5 ms, 2 -> 9.5 ms).
 constexpr int32_t kStatsPieces = 4;
-int64_t stats_pieces(int64_t P, int V) { return (P + 64 * V - 1) / (64 * V); }
-int64_t stats_blocks(int64_t pieces) { return (pieces + 8 * kStatsPieces - 1) / (8 * kStatsPieces) * 8; }
-int64_t stats_chunks(int64_t nb) { return (nb + kStatsChunk - 1) / kStatsChunk; }
+int64_t stats_blocks(int64_t P, int V) {
+  const int64_t pieces = (P + 64 * V - 1) / (64 * V);
+  return (pieces + 8 * kStatsPieces - 1) / (8 * kStatsPieces) * 8;
+}
 
 template <typename T>
-void launch_stats(MeanParams q, int nstates, int V, double* partials, double* out, hipStream_t st) {
-  q.tiles = stats_pieces(q.P, V);
-  const dim3 grid((unsigned)stats_blocks(q.tiles), nstates), block(64 * q.K);
-  const int64_t nb = grid.x, nc = stats_chunks(nb);
+void launch_stats(MeanParams q, int nstates, double* partials, double* out, hipStream_t st) {
+  constexpr int V = sizeof(T) == 2 ? 8 : 4;
+  const int64_t nb = stats_blocks(q.P, V), nc = (nb + kStatsChunk - 1) / kStatsChunk;
   const int32_t ns = kStatsSums(q.K);
-  double* level1 = partials + (size_t)nstates * ns * nb;
-  const size_t lds = (size_t)q.K * 64 * V * sizeof(float);
-  constexpr int VV = sizeof(T) == 2 ? 8 : 4;
-  if (V == 1) hipLaunchKernelGGL((k_replica_mean_stats<T, 1>), grid, block, lds, st, q, kStatsPieces, partials);
-  else hipLaunchKernelGGL((k_replica_mean_stats<T, VV>), grid, block, lds, st, q, kStatsPieces, partials);
-  hipLaunchKernelGGL(k_stats_reduce, dim3((unsigned)nc, nstates), dim3(256), 0, st, partials, nb, ns, level1);
-  hipLaunchKernelGGL(k_stats_finalize, dim3(nstates), dim3(256), 0, st, level1, (int32_t)nc, q.K, out);
+  q.tiles = nb;
+  const size_t lds = (size_t)2 * q.K * 64 * V * sizeof(float);
+  hipLaunchKernelGGL((k_replica_mean_stats<T, V, kStatsPieces>), tile_grid(nb, nstates), dim3(64 * q.K), lds, st, q,
+                     partials);
+  hipLaunchKernelGGL(k_stats_reduce, dim3((unsigned)nc, nstates), dim3(kStatsBlock), 0, st, partials, nb, ns);
+  hipLaunchKernelGGL(k_stats_finalize, dim3(nstates), dim3(kStatsBlock), 0, st, partials, nb, q.K, out);
 }
 
 // Doubles of the diagnostics scratch for up to 2 + N fp32 states and a bf16
-// x: each launch's partials and chunk sums, then the finalized rows of the
-// two launches.
+// x: each launch's partials, then the finalized rows of the two launches.
 size_t stats_scratch_doubles(const mtdao_config& c, size_t* fp32_part, size_t* bf16_part) {
   const int64_t ns = kStatsSums(c.replicas);
-  const int64_t nb32 = stats_blocks(stats_pieces(c.numel, vec_width(MTDAO_F32, c.numel)));
-  const int64_t nb16 = stats_blocks(stats_pieces(c.numel, vec_width(MTDAO_BF16, c.numel)));
-  *fp32_part = (size_t)(2 + c.n_moments) * ns * (nb32 + stats_chunks(nb32));
-  *bf16_part = c.param_dtype == MTDAO_BF16 ? (size_t)ns * (nb16 + stats_chunks(nb16)) : 0;
+  *fp32_part = (size_t)(2 + c.n_moments) * ns * stats_blocks(c.numel, slot(MTDAO_F32));
+  *bf16_part = c.param_dtype == MTDAO_BF16 ? (size_t)ns * stats_blocks(c.numel, slot(MTDAO_BF16)) : 0;
   return *fp32_part + *bf16_part + (size_t)2 * (2 + kMaxN) * kStatsStride;
 }
 
@@ -441,24 +411,25 @@ int launch_blocks(int64_t n) {
 }
 
 // Algorithm 4: averaged first moments feed the same step (SGDM only).
-void launch_sgdm_averaged_momenta(const mtdao_config& c, StepParams p, int V, uint32_t mask, hipStream_t st) {
-  dispatch_step(c, V, [&](auto form, auto n, auto xt, auto gt, auto vw) {
-    constexpr int FORM = decltype(form)::value, N = decltype(n)::value, VV = decltype(vw)::value;
+void launch_sgdm_averaged_momenta(const mtdao_config& c, StepParams p, uint32_t mask, hipStream_t st) {
+  dispatch_step(c, [&](auto form, auto n, auto xt, auto gt) {
+    constexpr int FORM = decltype(form)::value, N = decltype(n)::value, V = kStepV;
     if constexpr (FORM == kSgdm) {
       using XT = typename decltype(xt)::type;
       using GT = typename decltype(gt)::type;
-      if (c.replicas > 1 && c.replicas <= kWaveMaxK) {
+      constexpr int kLoad = (int)(sizeof(GT) + sizeof(XT)) + 4 * N;
+      const int K = c.replicas;
+      if (K > 1 && K <= kWaveMaxK) {
         // one wavefront per replica, one pass
-        const int64_t per = (int64_t)64 * VV;
-        p.tiles = (p.P + per - 1) / per;
-        hipLaunchKernelGGL((k_sgdm_averaged_momenta_waves<N, XT, GT, VV, kStepNT>), grid_for(p.tiles, 1),
-                           dim3(64 * c.replicas), 0, st, p, mask, c.replicas);
+        const int stages = std::max(1, __builtin_popcount(mask >> 1));
+        p.group = row_group(p.P);
+        hipLaunchKernelGGL((k_sgdm_averaged_momenta_waves<N, XT, GT, V, kStepNT>),
+                           group_grid((p.P + 64 * V - 1) / (64 * V), p.group), dim3(64 * K),
+                           wave_lds(stages, K, kLoad, p.P), st, p, mask, K);
         return;
       }
-      constexpr int C = piece_for(VV);
-      p.tiles = tiles_for<kBlock * VV, C>(p.P);
-      hipLaunchKernelGGL((k_sgdm_averaged_momenta<N, XT, GT, VV, kStepNT, C>), grid_for(p.tiles, 1), dim3(kBlock), 0,
-                         st, p, mask, c.replicas);
+      hipLaunchKernelGGL((k_sgdm_averaged_momenta<N, XT, GT, V, kStepNT>),
+                         tile_grid(tiles_for<kBlock * V, piece_for(V)>(p.P)), dim3(kBlock), 0, st, p, mask, K);
     }
   });
 }
@@ -706,9 +677,8 @@ StepParams prepare_step(mtdao_handle* h, const void* grads, float lr, float adop
   p.scale = nullptr;
   p.outer = outer_params(h);
   if (c.form != MTDAO_ADOPT && c.clip_rho > 0.0f) {
-    const int Vg = (P % 4 == 0) ? 4 : 1;  // 16-byte (fp32) or 8-byte (bf16) slots
-    if (c.grad_dtype == MTDAO_F32) launch_norm<float>(grads, P, c.replicas, Vg, h->norm_blocks, h->partials, st);
-    else launch_norm<uint16_t>(grads, P, c.replicas, Vg, h->norm_blocks, h->partials, st);
+    if (c.grad_dtype == MTDAO_F32) launch_norm<float>(grads, P, c.replicas, h->norm_blocks, h->partials, st);
+    else launch_norm<uint16_t>(grads, P, c.replicas, h->norm_blocks, h->partials, st);
     hipLaunchKernelGGL(k_clip_finalize, dim3(c.replicas), dim3(kFinalizeBlock), 0, st, h->partials, h->norm_blocks,
                        (double)c.clip_rho, h->scale);
     p.scale = h->scale;
@@ -716,19 +686,15 @@ StepParams prepare_step(mtdao_handle* h, const void* grads, float lr, float adop
   return p;
 }
 
-// One vector width for every buffer the step touches: 4 elements when every
-// row start keeps 16-byte (fp32) and 8-byte (bf16) alignment, else 1.
-int step_vec_width(const mtdao_config& c) { return (c.numel % 4 == 0) ? 4 : 1; }
-
 bool adopt_first_update(const mtdao_config& c, int64_t s) {
   return c.form == MTDAO_ADOPT && c.adopt_order == MTDAO_ADOPT_PREV && s == 1;
 }
 
 void launch_adopt_first(mtdao_handle* h, const void* grads, hipStream_t st) {
   const mtdao_config& c = h->cfg;
-  const int Vi = (c.numel % 4 == 0) ? 4 : 1;
-  if (c.grad_dtype == MTDAO_F32) launch_adopt_init<float>(grads, h->v, c.numel, c.replicas, Vi, st);
-  else launch_adopt_init<uint16_t>(grads, h->v, c.numel, c.replicas, Vi, st);
+  const int64_t n = c.numel * c.replicas;
+  if (c.grad_dtype == MTDAO_F32) launch_adopt_init<float>(grads, h->v, n, st);
+  else launch_adopt_init<uint16_t>(grads, h->v, n, st);
 }
 
 void launch_means(mtdao_handle* h, uint32_t m, bool outer_update, hipStream_t st) {
@@ -748,12 +714,12 @@ void launch_means(mtdao_handle* h, uint32_t m, bool outer_update, hipStream_t st
   for (int j = 0; j < c.n_moments; ++j)
     if (m & (1u << (j + 1))) mp.state[n++] = h->u[j];
   if (h->v && (m & (1u << (c.n_moments + 1)))) mp.state[n++] = h->v;
-  if (n > 0) launch_mean<float>(mp, n, vec_width(MTDAO_F32, c.numel), st);
+  if (n > 0) launch_mean<float>(mp, n, st);
   if ((m & 1u) && c.param_dtype == MTDAO_BF16) {
     MeanParams xp = mp;
     xp.state[0] = h->x;
     xp.outer_state = outer_update ? 0 : -1;
-    launch_mean<uint16_t>(xp, 1, vec_width(MTDAO_BF16, c.numel), st);
+    launch_mean<uint16_t>(xp, 1, st);
   }
 }
 
@@ -782,9 +748,9 @@ int32_t step_sync_launch(mtdao_handle* h, const void* grads, float lr, float ado
   } else if (work == 0) {
     launch_step(c, p, st);
   } else if (c.sync_order == MTDAO_SYNC_MOMENTA_IN_STEP && (work & ~1u) != 0) {
-    launch_sgdm_averaged_momenta(c, p, step_vec_width(c), work, st);
+    launch_sgdm_averaged_momenta(c, p, work, st);
   } else {
-    launch_step_sync(c, p, step_vec_width(c), work, st);
+    launch_step_sync(c, p, work, st);
   }
   return hip_check(&h->err, hipGetLastError(), "mtdao_step_sync launch");
 }
@@ -920,14 +886,14 @@ int32_t run_sync_stats(mtdao_handle* h, uint32_t mask, uint32_t* applied_mask, d
     ids[n] = c.n_moments + 1;
     mp.state[n++] = h->v;
   }
-  if (n > 0) launch_stats<float>(mp, n, vec_width(MTDAO_F32, c.numel), partials, out, st);
+  if (n > 0) launch_stats<float>(mp, n, partials, out, st);
   const bool bf16_x = (m & 1u) && c.param_dtype == MTDAO_BF16;
   if (bf16_x) {
     MeanParams q = mp;
     std::memset(q.state, 0, sizeof q.state);
     q.state[0] = h->x;
     q.outer_state = h->x_outer ? 0 : -1;
-    launch_stats<uint16_t>(q, 1, vec_width(MTDAO_BF16, c.numel), part_x, out + nslots * kStatsStride, st);
+    launch_stats<uint16_t>(q, 1, part_x, out + nslots * kStatsStride, st);
   }
   r = hip_check(&h->err, hipGetLastError(), "mtdao_sync_stats launch");
   if (r != MTDAO_OK) return r;
