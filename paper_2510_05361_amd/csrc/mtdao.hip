@@ -422,6 +422,11 @@ void launch_sgdm_averaged_momenta(const mtdao_config& c, StepParams p, uint32_t 
       if (K > 1 && K <= kWaveMaxK) {
         // one wavefront per replica, one pass
         const int stages = std::max(1, __builtin_popcount(mask >> 1));
+        if (K > 8 && p.P % V == 0) {
+          hipLaunchKernelGGL((k_sgdm_averaged_momenta_waves_rounds<N, XT, GT, V, kStepNT>),
+                             tile_grid((p.P + 64 * V - 1) / (64 * V)), dim3(64 * K), 0, st, p, mask, K);
+          return;
+        }
         p.group = row_group(p.P);
         hipLaunchKernelGGL((k_sgdm_averaged_momenta_waves<N, XT, GT, V, kStepNT>),
                            group_grid((p.P + 64 * V - 1) / (64 * V), p.group), dim3(64 * K),

@@ -47,6 +47,13 @@ def test_row_lengths(form, K, x, g, P):
     _check(_workload(form, P, K, x, g), f"rows-{form}-{K}-{x}-{g}-{P}")
 
 
+@pytest.mark.parametrize("K", [12, 16])
+def test_every_state_staged(K):
+    """Five due states of 12 and 16 replicas exchanged at once (s = 12): the
+    largest LDS request of the suite's forms, 80 KiB."""
+    _check(_workload("adam", 1027, K, steps=12), f"staged-{K}")
+
+
 @pytest.mark.parametrize("form,K,P,x", [("adam", 3, 1_500_003, "f32"), ("sgdm", 8, 1_000_005, "bf16")])
 def test_limited_residency(form, K, P, x):
     """More than 64 MB loaded per launch."""
