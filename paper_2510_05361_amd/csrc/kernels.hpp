@@ -1592,16 +1592,18 @@ constexpr int kStatsStride = 4 + 2 * kStatsMaxK;  // doubles per state (layout i
 // them and ran 30% slower).  The next piece's loads are issued before a
 // piece's exchange, and consecutive pieces use two LDS buffers in turn, so a
 // piece takes two barriers.  Each wave keeps fp64 sums for its own replica
-// (wave 0 also those of cbar and xo): a lane forms the V products of a piece
-// in fp32 (one rounding each, about 6e-8 relative) and adds their fp32 sum
-// to the fp64 sums, which keeps the fp64 work per element to a fraction of
-// an operation.  The workgroup writes its kStatsSums(K) sums, contiguous, to
+// (wave 0 also those of cbar and xo).  Rows of whole 16-byte slots: a lane
+// forms the V products of a piece in fp32 (one rounding each, about 6e-8
+// relative) and adds their fp32 sum to the fp64 sums, which keeps the fp64
+// work per element to a fraction of an operation.  Other rows (EACH) add
+// every product, rounded to fp32, to the fp64 sums by itself.  The workgroup
+// writes its kStatsSums(K) sums, contiguous, to
 // partials[state][workgroup][sum]:
 //   0 ||cbar||^2, 1 sum_m ||c^m - cbar||^2, 2 ||xo||^2,
 //   3 + m ||c^m||^2, 3 + K + m <c^m, cbar>.
 __host__ __device__ constexpr int kStatsSums(int K) { return 3 + 2 * K; }
 
-template <typename T, int V, int Q>
+template <typename T, int V, int Q, bool EACH>
 __global__ __launch_bounds__(64 * kStatsMaxK) void k_replica_mean_stats(MeanParams p, double* __restrict__ partials) {
   constexpr int E = 64 * V;
   extern __shared__ __align__(16) float stage[];  // [2][K][64 V]
@@ -1654,28 +1656,35 @@ __global__ __launch_bounds__(64 * kStatsMaxK) void k_replica_mean_stats(MeanPara
     // store first, then reduce the diagnostics while the stores drain
     if (in_row >= E) store_n<true, T, V, true>(row + e0, o, n, out);
     else store_n<false, T, V, true>(row + e0, o, n, out);
-    // the piece's V terms in fp32, added to the fp64 sums once per piece
-    // (values, means and outer parameters beyond the row are 0)
+    // the terms of the piece's V elements (values, means and outer parameters
+    // beyond the row are 0): each product rounded to fp32 once, then added to
+    // the fp64 sums (EACH) or to an fp32 sum that joins them once per piece
     float f_sq = 0.0f, f_dot = 0.0f, f_var = 0.0f, f_mean = 0.0f, f_ref = 0.0f;
 #pragma unroll
     for (int t = 0; t < V; ++t) {
       const float cbar = outer ? xo[t] - mean[t] : mean[t];
       const float c = outer ? xo[t] - a[t] : a[t];
       const float dv = a[t] - mean[t];  // c - cbar up to sign
-      f_sq = __builtin_fmaf(c, c, f_sq);
-      f_dot = __builtin_fmaf(c, cbar, f_dot);
-      f_var = __builtin_fmaf(dv, dv, f_var);
+      auto add = [&](double& sum, float& part, float p, float q) {
+        if constexpr (EACH) sum += (double)(p * q);
+        else part = __builtin_fmaf(p, q, part);
+      };
+      add(a_sq, f_sq, c, c);
+      add(a_dot, f_dot, c, cbar);
+      add(a_var, f_var, dv, dv);
       if (m == 0) {
-        f_mean = __builtin_fmaf(cbar, cbar, f_mean);
-        if (outer) f_ref = __builtin_fmaf(xo[t], xo[t], f_ref);
+        add(a_mean, f_mean, cbar, cbar);
+        if (outer) add(a_ref, f_ref, xo[t], xo[t]);
       }
     }
-    a_sq += (double)f_sq;
-    a_dot += (double)f_dot;
-    a_var += (double)f_var;
-    if (m == 0) {
-      a_mean += (double)f_mean;
-      if (outer) a_ref += (double)f_ref;
+    if constexpr (!EACH) {
+      a_sq += (double)f_sq;
+      a_dot += (double)f_dot;
+      a_var += (double)f_var;
+      if (m == 0) {
+        a_mean += (double)f_mean;
+        if (outer) a_ref += (double)f_ref;
+      }
     }
 #pragma unroll
     for (int t = 0; t < V; ++t) a[t] = nx[t];

@@ -383,8 +383,9 @@ void launch_stats(MeanParams q, int nstates, double* partials, double* out, hipS
   const int32_t ns = kStatsSums(q.K);
   q.tiles = nb;
   const size_t lds = (size_t)2 * q.K * 64 * V * sizeof(float);
-  hipLaunchKernelGGL((k_replica_mean_stats<T, V, kStatsPieces>), tile_grid(nb, nstates), dim3(64 * q.K), lds, st, q,
-                     partials);
+  auto go = [&](auto kernel) { hipLaunchKernelGGL(kernel, tile_grid(nb, nstates), dim3(64 * q.K), lds, st, q, partials); };
+  if (q.P % V == 0) go(k_replica_mean_stats<T, V, kStatsPieces, false>);
+  else go(k_replica_mean_stats<T, V, kStatsPieces, true>);
   hipLaunchKernelGGL(k_stats_reduce, dim3((unsigned)nc, nstates), dim3(kStatsBlock), 0, st, partials, nb, ns);
   hipLaunchKernelGGL(k_stats_finalize, dim3(nstates), dim3(kStatsBlock), 0, st, partials, nb, q.K, out);
 }

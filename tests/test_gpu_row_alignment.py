@@ -15,6 +15,8 @@ import torch
 
 import synth
 from gpu_harness import compare, free, log, run_gpu, run_oracle, run_oracle_parallel
+from paper_2510_05361_amd import mtdao as abi
+from paper_2510_05361_amd.optimizer import MtdaoOptimizer
 
 pytestmark = pytest.mark.gpu
 
@@ -58,3 +60,26 @@ def test_every_state_staged(K):
 def test_limited_residency(form, K, P, x):
     """More than 64 MB loaded per launch."""
     _check(_workload(form, P, K, x, x, steps=4), f"resident-{form}-{K}-{P}", run_oracle_parallel)
+
+
+@pytest.mark.parametrize("dtype,P", [("f32", 1027), ("f32", 262_145), ("bf16", 1028), ("bf16", 1031),
+                                     ("bf16", 262_145)])
+def test_ragged_diagnostics_sum_each_product_in_fp64(dtype, P):
+    """Rows that are no whole number of 16-byte slots add every product to
+    the fp64 sums by itself.  Identical workers with the values 4096, 1, 1, 1
+    in turn: each product (2^24 or 1) and every fp64 sum of them (integers
+    below 2^53) is exact, so the diagnostics must be the integers themselves,
+    while an fp32 sum of a slot would lose every 1 beside a 2^24."""
+    K = 4
+    cfg = abi.make_config("sgdm", K, (0.9,), (0.9,), P, param_dtype=dtype, grad_dtype=dtype)
+    row = torch.ones(P, device="cuda")
+    row[::4] = 4096.0
+    log(f"case exact diagnostics {dtype} P={P}")
+    opt = MtdaoOptimizer(cfg, torch.device("cuda"), x0=row)
+    stats = opt.sync_stats(1)[1][0]
+    big = (P + 3) // 4
+    want = float((big << 24) + P - big)
+    assert stats[abi.MTDAO_STAT_MEAN_SQ] == want and stats[abi.MTDAO_STAT_VARIANCE] == 0.0
+    for m in range(K):
+        assert stats[abi.MTDAO_STAT_WORKER_SQ + m] == want and stats[abi.MTDAO_STAT_WORKER_DOT + m] == want
+    opt.close()
