@@ -1,0 +1,61 @@
+"""Launch shapes of the tiled kernels (CPU: the host functions of kernels.hpp
+in a small program; nothing is launched).
+
+A launch's x extent holds fewer than 2^32 threads, so many tiles go along x
+and y.  Every tile needs a workgroup, and workgroups without a tile cost:
+they take the LDS and the places of those with work.
+"""
+
+from __future__ import annotations
+
+import os
+import subprocess
+
+import pytest
+
+from paper_2510_05361_amd import build
+
+SOURCE = r"""
+#include <cstdio>
+#include "kernels.hpp"
+int main() {
+  long long tiles;
+  int group;
+  while (scanf("%lld %d", &tiles, &group) == 2) {
+    const dim3 g = group == 0 ? mtdao::tile_grid(tiles, 3) : mtdao::group_grid(tiles, group, 3);
+    printf("%u %u %u\n", g.x, g.y, g.z);
+  }
+}
+"""
+ONE_ROW = 1 << 21  # tiles of the largest one-dimensional launch
+# around one and several rows, 1.31B x 4 (pieces), 354M x 16 (step tiles), 2^40 elements
+TILES = [1, 7, 8, 16, 58_296, 1_381_252, ONE_ROW - 1, ONE_ROW, ONE_ROW + 1, ONE_ROW + 8, 2 * ONE_ROW,
+         2 * ONE_ROW + 1, 3 * ONE_ROW + 17, 5_121_800, 11_050_016, 1 << 31, (1 << 32) + 1]
+
+
+@pytest.fixture(scope="module")
+def grids(tmp_path_factory):
+    if not os.path.exists(build.HIPCC):
+        pytest.skip("hipcc not available")
+    d = tmp_path_factory.mktemp("shapes")
+    src, exe = d / "shapes.hip", d / "shapes"
+    src.write_text(SOURCE)
+    flags = [f for f in build.FLAGS if f not in ("-shared", "-fPIC", "-O3")]
+    subprocess.run([build.HIPCC, *flags, "-O1", "-w", "-I", os.path.dirname(build.SRC), "-o", str(exe), str(src)],
+                   check=True, stderr=subprocess.DEVNULL)
+    cases = [(t, g) for t in TILES for g in (0, 1, 8)]
+    out = subprocess.run([str(exe)], input="".join(f"{t} {g}\n" for t, g in cases), capture_output=True, text=True,
+                         check=True, timeout=60).stdout
+    return dict(zip(cases, (tuple(int(v) for v in line.split()) for line in out.splitlines())))
+
+
+@pytest.mark.parametrize("group", [0, 1, 8])
+@pytest.mark.parametrize("tiles", TILES)
+def test_grid_covers_the_tiles_and_little_more(grids, tiles, group):
+    x, y, z = grids[tiles, group]
+    span = 1 if group < 2 else 8 * group  # pieces are taken in whole groups of the 8 XCDs
+    whole = (tiles + span - 1) // span * span
+    assert z == 3 and x * 1024 < 1 << 32 and 1 <= y <= 65535
+    assert x * y >= whole
+    # x a multiple of 16 keeps a tile's XCD and parity; at most that rounding is empty
+    assert (y == 1 and x == whole) or (x % 16 == 0 and x * y - whole < 17 * y)
