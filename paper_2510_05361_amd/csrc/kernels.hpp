@@ -275,7 +275,7 @@ __device__ __forceinline__ int64_t launch_tile() { return (int64_t)blockIdx.y * 
 // parity are those of its number, and beyond that rounding every workgroup
 // has a tile.  (Whole rows of 2^21 workgroups left 23 % of those of 1.31B x 4
 // empty, each with its place on a CU and its LDS: fused step with x due
-// 40.3 ms, mean of one state 7.25 ms, against 36.7 and 6.58 ms.)
+// 40.3 ms, mean of one state 7.25 ms, against 36.7 and 6.4 ms.)
 inline dim3 tile_grid(int64_t tiles, int32_t nz = 1) {
   const int64_t maxx = INT64_C(1) << 21;
   if (tiles < 1) tiles = 1;
@@ -1370,6 +1370,7 @@ struct MeanParams {
   void* state[kMaxMeanStates];  // [K][P] buffers of one storage type
   int64_t P;
   int64_t tiles;                // k_replica_mean_stats: workgroups
+  double rk;                    // k_replica_mean_waves: 1 / K
   int32_t K;
   int32_t group;                // group_piece
   int32_t outer_state;          // index of x in state[] when OuterOpt applies, else -1
@@ -1427,22 +1428,30 @@ __global__ __launch_bounds__(kBlock) void k_replica_mean(MeanParams p) {
 // w + (R - 1) W (W = K / R waves), the K pieces meet in LDS, all waves share
 // the means (mean_add / mean_of in replica order, so every element gets
 // exactly the value k_replica_mean gives), the OuterOpt runs element by
-// element on x, and each wave stores the mean to its rows.  Each wave then
-// issues R loads and R stores per piece, as a plain copy does; a thread that
-// walks all K rows of its columns (k_replica_mean) ran the K = 4 mean at 74%
-// of the HBM peak on MI355X, this kernel at 82.6%.
-template <typename T, int V, bool NT, int R = 1>
+// element on x (O: one of the launch's states takes it), and each wave stores
+// the mean to its rows.  Each wave then issues R loads and R stores per
+// piece, as a plain copy does; a thread that walks all K rows of its columns
+// (k_replica_mean) ran the K = 4 mean at 74% of the HBM peak on MI355X, this
+// kernel runs at 82% (1.31B x 4 fp32: 6.37 ms).  A wave has one access per
+// piece in flight, so whatever stands between its load and its store costs
+// bandwidth: with 1 / K divided or loaded between the barriers, the OuterOpt
+// in the same code, a signed element count that was divided into stages, and
+// the rows' sum unrolled by four (K = 4 has three to add) the same pass took
+// 6.57 ms.
+template <typename T, int V, bool NT, bool O, int R = 1>
 __global__ __launch_bounds__(64 * kWaveMaxK / R) void k_replica_mean_waves(MeanParams p) {
   constexpr int E = 64 * V, U = kPieceMaxU * V / 4;
   extern __shared__ __align__(16) float stage[];
-  const int32_t K = p.K, W = K / R;
+  const int32_t K = p.K, W = K / R, lane = threadIdx.x & 63;
   const int32_t w = __builtin_amdgcn_readfirstlane((int32_t)(threadIdx.x >> 6));
   const int64_t e0 = group_piece(p.group) * E;
-  const uint32_t o = (threadIdx.x & 63) * V;
+  const uint32_t o = lane * V;
   const int32_t in_row = left_in_row(e0, p.P), n = in_row - (int32_t)o;
   if (in_row == 0) return;  // a whole workgroup past the row
   T* s = reinterpret_cast<T*>(p.state[blockIdx.z]) + e0;
-  const bool outer = (int32_t)blockIdx.z == p.outer_state;
+  const bool outer = O && (int32_t)blockIdx.z == p.outer_state;
+  double rk = p.rk;
+  asm("" : "+s"(rk));  // loaded here, not between the barriers
 
   auto piece = [&](auto full) {
     constexpr bool F = decltype(full)::value;
@@ -1454,7 +1463,26 @@ __global__ __launch_bounds__(64 * kWaveMaxK / R) void k_replica_mean_waves(MeanP
 #pragma unroll
     for (int r = 0; r < R; ++r) lds_put<V>(stage + (w + r * W) * E + o, a[r]);
     __syncthreads();
-    average_stages<E>(stage, K, 1, in_row, 1.0 / (double)K, p.outer, outer, ahead, e0);
+    // run r of 64 elements to wave r mod W
+    auto average = [&](uint32_t r, auto&& put) {
+      const int32_t j = (int32_t)(r * 64) + lane;
+      if (!F && j >= in_row) return;
+      const float s0 = stage[j];
+      double d = 0.0;
+#pragma unroll 3
+      for (int32_t q = 1; q < K; ++q) mean_add(d, stage[q * E + j], s0);
+      stage[j] = put(j, mean_of(s0, d, rk));
+    };
+    if (outer) {
+#pragma unroll
+      for (int i = 0; i < U; ++i)
+        if (w + i * W < E / 64)
+          average(w + i * W, [&](int32_t j, float a) {
+            return outer_element(p.outer, e0 + j, ahead.xo[i], ahead.mom[i], a);
+          });
+    } else {
+      for (uint32_t r = w; r < E / 64; r += W) average(r, [](int32_t, float a) { return a; });
+    }
     __syncthreads();
     float b[V];
     lds_get<V>(stage + o, b);

@@ -352,8 +352,15 @@ void launch_mean(MeanParams p, int nstates, hipStream_t st) {
     const dim3 grid = group_grid((p.P + 64 * V - 1) / (64 * V), p.group, nstates);
     const dim3 block(64 * (two ? p.K / 2 : p.K));
     const size_t lds = (size_t)p.K * 64 * V * sizeof(float);
-    if (two) hipLaunchKernelGGL((k_replica_mean_waves<T, V, kMeanNT, 2>), grid, block, lds, st, p);
-    else hipLaunchKernelGGL((k_replica_mean_waves<T, V, kMeanNT>), grid, block, lds, st, p);
+    auto go = [&](auto kernel) { hipLaunchKernelGGL(kernel, grid, block, lds, st, p); };
+    if (p.outer_state < 0) {
+      if (two) go(k_replica_mean_waves<T, V, kMeanNT, false, 2>);
+      else go(k_replica_mean_waves<T, V, kMeanNT, false>);
+    } else if (two) {
+      go(k_replica_mean_waves<T, V, kMeanNT, true, 2>);
+    } else {
+      go(k_replica_mean_waves<T, V, kMeanNT, true>);
+    }
     return;
   }
   // K = 1 (an outer step only) and K > kWaveMaxK: one thread per column
@@ -709,6 +716,7 @@ void launch_means(mtdao_handle* h, uint32_t m, bool outer_update, hipStream_t st
   std::memset(&mp, 0, sizeof mp);
   mp.P = c.numel;
   mp.K = c.replicas;
+  mp.rk = 1.0 / (double)c.replicas;
   mp.outer_state = -1;
   mp.outer = outer_params(h);
   // fp32 moment states (and fp32 x) in one launch, bf16 x in its own
