@@ -310,7 +310,7 @@ inline dim3 group_grid(int64_t pieces, int32_t group, int32_t nz = 1) {
 // about 40 KiB of loads per CU ran fastest for every mix of streams, against
 // up to 192 KiB at full occupancy.  A launch limits the workgroups that a CU
 // holds at once by asking for LDS it does not use: 160 KiB per CU, in units
-// of 1280 bytes; a workgroup may ask for 51 units, which leaves two.
+// of 1280 bytes; the limit asks for 51 of them at most, which leaves two.
 // Passes that load less than kResidentMin bytes hit the 256 MB MALL more than the
 // HBM and keep every wave that the CUs hold (Adam N = 3, 4 replicas, limited
 // against not: 88 MB 15.5 us against 15.1 us, 176 MB 29.3 us against
@@ -318,14 +318,21 @@ inline dim3 group_grid(int64_t pieces, int32_t group, int32_t nz = 1) {
 constexpr int64_t kResidentMin = INT64_C(64) << 20;
 constexpr size_t resident_lds(int n) { return (size_t)(128 / n > 51 ? 51 : 128 / n) * 1280; }
 
-// Workgroups per CU of the fused step with one wave per replica, whose
-// barriers ask for more waves than the plain step: 12 waves, at least two
-// workgroups.  K > 8 has two by its size (one took 0.86 to 0.96 of the
-// rate).  Unlimited -> limited on the same buffers of an MI355X: K = 4 Adam
-// N = 3 with x due 16.8M 515 -> 473 us, all due 354M 11.39 -> 10.55 ms;
-// K = 6 with x due 40M 1947 -> 1815 us; K = 8 ADOPT bf16 all due 60M
-// 2652 -> 2471 us; K = 2 all due 60M 871 -> 847 us.
-constexpr int wave_resident(int K) { return 12 / K > 2 ? 12 / K : 2; }
+// Workgroups per CU of the fused step with one wave per replica, for `bytes`
+// loaded per element.  Its barriers ask for more bytes in flight than the
+// plain step, and the fewer streams a form has the more waves those take: 12
+// waves for six 4-byte streams (72 KiB of loads), 28 for two (56 KiB).  At
+// least two workgroups, which K > 8 has by its size (one took 0.86 to 0.96 of
+// the rate), unless their LDS does not allow it (more than 80 KiB each: six
+// due states of 14 or more rows).  All due, 1.6 GB loaded, same buffers of an
+// MI355X, unlimited / as here: SGDM N = 1 K = 4 457 / 428 us (12 waves for
+// every form took 474), in bf16 K = 2 439 / 438 us (687) and K = 6
+// 479 / 491 us (676), Adam N = 1 K = 4 499 / 457 us (484), Adam N = 2 K = 4
+// 500 / 472 us; Adam N = 3 354M x 4 11.39 / 10.54 ms.
+constexpr int wave_resident(int K, int bytes) {
+  const int waves = bytes <= 8 ? 28 : bytes <= 10 ? 24 : bytes <= 14 ? 18 : bytes <= 18 ? 16 : bytes <= 22 ? 14 : 12;
+  return waves / K > 2 ? waves / K : 2;
+}
 
 // The local step's workgroups for `bytes` loaded per element (four elements
 // per lane): two waves each, for steps of the limit that are fine enough,

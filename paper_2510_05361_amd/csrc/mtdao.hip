@@ -247,7 +247,7 @@ constexpr int kStepV = 4;
 // and enough that a CU holds wave_resident(K) workgroups.
 size_t wave_lds(int stages, int K, int bytes, int64_t P) {
   const size_t need = (size_t)stages * K * 64 * kStepV * sizeof(float);
-  return P * K * bytes >= kResidentMin ? std::max(need, resident_lds(wave_resident(K))) : need;
+  return P * K * bytes >= kResidentMin ? std::max(need, resident_lds(wave_resident(K, bytes))) : need;
 }
 
 // The local step alone, over the K P elements of every buffer as flat

@@ -18,9 +18,13 @@ from paper_2510_05361_amd import build
 SOURCE = r"""
 #include <cstdio>
 #include "kernels.hpp"
-int main() {
+int main(int argc, char** argv) {
   long long tiles;
   int group;
+  if (argc > 1) {  // workgroups per CU of the fused step: replicas, bytes loaded per element
+    while (scanf("%lld %d", &tiles, &group) == 2) printf("%d\n", mtdao::wave_resident((int)tiles, group));
+    return 0;
+  }
   while (scanf("%lld %d", &tiles, &group) == 2) {
     const dim3 g = group == 0 ? mtdao::tile_grid(tiles, 3) : mtdao::group_grid(tiles, group, 3);
     printf("%u %u %u\n", g.x, g.y, g.z);
@@ -34,7 +38,7 @@ TILES = [1, 7, 8, 16, 58_296, 1_381_252, ONE_ROW - 1, ONE_ROW, ONE_ROW + 1, ONE_
 
 
 @pytest.fixture(scope="module")
-def grids(tmp_path_factory):
+def program(tmp_path_factory):
     if not os.path.exists(build.HIPCC):
         pytest.skip("hipcc not available")
     d = tmp_path_factory.mktemp("shapes")
@@ -43,10 +47,17 @@ def grids(tmp_path_factory):
     flags = [f for f in build.FLAGS if f not in ("-shared", "-fPIC", "-O3")]
     subprocess.run([build.HIPCC, *flags, "-O1", "-w", "-I", os.path.dirname(build.SRC), "-o", str(exe), str(src)],
                    check=True, stderr=subprocess.DEVNULL)
-    cases = [(t, g) for t in TILES for g in (0, 1, 8)]
-    out = subprocess.run([str(exe)], input="".join(f"{t} {g}\n" for t, g in cases), capture_output=True, text=True,
-                         check=True, timeout=60).stdout
-    return dict(zip(cases, (tuple(int(v) for v in line.split()) for line in out.splitlines())))
+
+    def run(cases, *args):
+        out = subprocess.run([str(exe), *args], input="".join(f"{a} {b}\n" for a, b in cases), capture_output=True,
+                             text=True, check=True, timeout=60).stdout
+        return dict(zip(cases, (tuple(int(v) for v in line.split()) for line in out.splitlines())))
+    return run
+
+
+@pytest.fixture(scope="module")
+def grids(program):
+    return program([(t, g) for t in TILES for g in (0, 1, 8)])
 
 
 @pytest.mark.parametrize("group", [0, 1, 8])
@@ -59,3 +70,13 @@ def test_grid_covers_the_tiles_and_little_more(grids, tiles, group):
     assert x * y >= whole
     # x a multiple of 16 keeps a tile's XCD and parity; at most that rounding is empty
     assert (y == 1 and x == whole) or (x % 16 == 0 and x * y - whole < 17 * y)
+
+
+def test_fused_step_keeps_loads_in_flight(program):
+    """The limit of workgroups per CU leaves every form of the fused step at
+    least 40 KiB of loads in flight (four elements per lane), also those with
+    few streams; one that left them 24 KiB took their rate down by a third."""
+    forms = [(k, b) for k in range(2, 9) for b in range(8, 29, 2)]
+    resident = program(forms, "resident")
+    low = {f: n for f, (n,) in resident.items() if n * f[0] * 64 * 4 * f[1] < 40 << 10 and n * f[0] < 32 - f[0]}
+    assert not low, low
