@@ -286,20 +286,23 @@ inline dim3 tile_grid(int64_t tiles, int32_t nz = 1) {
 
 // The piece of this workgroup in the wave-per-replica kernels, which take
 // one piece of every row.  group = 1: pieces in order, so the XCDs take one
-// in turn.  group = G > 1: each XCD takes G consecutive pieces with G
-// workgroups that follow one another on it.  Rows that do not start on
-// 128-byte lines share a line between neighbouring pieces; written from two
-// XCDs' L2 caches each half goes to memory by itself, so such rows take
-// G = 8 (row_group): 16.8M + 37 x 4 Adam with x due 610 -> 550 us, 30M + 1
-// x 8 ADOPT bf16 with all due 1665 -> 1494 us; G = 16 and 32 were equal.
-// Rows on whole lines take G = 1, which spreads the XCDs best (354M x 4 all
-// due 10.9 ms, G = 8 11.3 ms).  Pieces past the row have no elements.
+// in turn.  group = 8: each XCD takes 8 consecutive pieces with 8 workgroups
+// that follow one another on it.  Rows that do not start on 128-byte lines
+// share a line between neighbouring pieces; written from two XCDs' L2 caches
+// each half goes to memory by itself, so such rows take group = 8
+// (row_group; `bytes` of an element, 4 for the fused kernels, most of whose
+// streams are fp32).  group = 1 -> 8 on the same buffers: fused Adam N = 2,
+// K = 4, x due, 30M + 1 927 -> 858 us, 30M + 8 895 -> 841 us, 30M + 16
+// 806 -> 794 us, 30M + 32 (whole lines) 749 -> 774 us; mean K = 4, bf16,
+// 80M + 32 243 -> 225 us, fp32, 40M + 4 227 -> 209 us; K = 16, fp32, 40M + 32
+// (whole lines) 888 -> 926 us.  Groups of 16 and 32 were equal to 8.  Pieces
+// past the row have no elements.
 __device__ __forceinline__ int64_t group_piece(int32_t group) {
   const int64_t t = launch_tile();
   if (group == 1) return t;
-  return t / (8 * group) * (8 * group) + (t & 7) * group + (t >> 3) % group;
+  return (t & ~(int64_t)63) | ((t & 7) << 3) | ((t >> 3) & 7);
 }
-inline int32_t row_group(int64_t P) { return P % 64 == 0 ? 1 : 8; }
+inline int32_t row_group(int64_t P, int bytes) { return P * bytes % 128 == 0 ? 1 : 8; }
 inline dim3 group_grid(int64_t pieces, int32_t group, int32_t nz = 1) {
   const int64_t span = group == 1 ? 1 : 8 * group;
   return tile_grid((pieces + span - 1) / span * span, nz);

@@ -300,7 +300,7 @@ void launch_step_sync(const mtdao_config& c, StepParams p, uint32_t mask, hipStr
         go(k_local_step_sync_waves_rounds<FORM, N, XT, GT, V, kStepNT, kPrev>);
         return;
       }
-      p.group = row_group(p.P);
+      p.group = row_group(p.P, sizeof(float));
       const dim3 grid = group_grid(pieces, p.group);
       const size_t lds = wave_lds(__builtin_popcount(mask), K, kLoad, p.P);
       auto go = [&](auto kernel) { hipLaunchKernelGGL(kernel, grid, block, lds, st, p, mask, K); };
@@ -348,7 +348,7 @@ void launch_mean(MeanParams p, int nstates, hipStream_t st) {
     // (measured on MI355X at K = 8: bf16 x 72% of peak with two rows per
     // wave against 68% with one, fp32 states 75.7% against 77.2%)
     const bool two = p.K % 2 == 0 && (p.K > 8 || (p.K == 8 && sizeof(T) == 2));
-    p.group = row_group(p.P);
+    p.group = row_group(p.P, sizeof(T));
     const dim3 grid = group_grid((p.P + 64 * V - 1) / (64 * V), p.group, nstates);
     const dim3 block(64 * (two ? p.K / 2 : p.K));
     const size_t lds = (size_t)p.K * 64 * V * sizeof(float);
@@ -435,7 +435,7 @@ void launch_sgdm_averaged_momenta(const mtdao_config& c, StepParams p, uint32_t 
                              tile_grid((p.P + 64 * V - 1) / (64 * V)), dim3(64 * K), 0, st, p, mask, K);
           return;
         }
-        p.group = row_group(p.P);
+        p.group = row_group(p.P, sizeof(float));
         hipLaunchKernelGGL((k_sgdm_averaged_momenta_waves<N, XT, GT, V, kStepNT>),
                            group_grid((p.P + 64 * V - 1) / (64 * V), p.group), dim3(64 * K),
                            wave_lds(stages, K, kLoad, p.P), st, p, mask, K);
