@@ -1628,7 +1628,7 @@ constexpr int kStatsStride = 4 + 2 * kStatsMaxK;  // doubles per state (layout i
 
 // The replica mean of the wave-per-replica kernel (same pieces, same
 // mean_add / mean_of order, same values) plus, from the values before
-// averaging, the averaging diagnostics of state blockIdx.y: ||cbar||^2,
+// averaging, the averaging diagnostics of state blockIdx.z: ||cbar||^2,
 // sum_m ||c^m - cbar||^2, ||xo||^2, ||c^m||^2 and <c^m, cbar>, with
 // c^m = S^m, or c^m = xo - x^m for x under a Nesterov OuterOpt.
 // blockDim = 64 K (1 <= K <= kStatsMaxK), dynamic LDS of 2 K * 64 V floats.
@@ -1638,7 +1638,12 @@ constexpr int kStatsStride = 4 + 2 * kStatsMaxK;  // doubles per state (layout i
 // the plain mean (a fixed grid of workgroups striding over the row scattered
 // them and ran 30% slower).  The next piece's loads are issued before a
 // piece's exchange, and consecutive pieces use two LDS buffers in turn, so a
-// piece takes two barriers.  Each wave keeps fp64 sums for its own replica
+// piece takes two barriers.  That the loads stay in flight over the exchange
+// takes code without branches between them and their use (the last pieces of
+// a row have code of their own) and slots kept as stored: with both kinds of
+// piece and the conversion in one body the compiler waited for the next
+// piece at once (fp32, 16M x 4 one state 127 us, now 113; 4M x 16 175 -> 122;
+// bf16 92 -> 71 and 124 -> 78 us, at 78 registers against 56 now).  Each wave keeps fp64 sums for its own replica
 // (wave 0 also those of cbar and xo).  Rows of whole 16-byte slots: a lane
 // forms the V products of a piece in fp32 (one rounding each, about 6e-8
 // relative) and adds their fp32 sum to the fp64 sums, which keeps the fp64
@@ -1650,8 +1655,19 @@ constexpr int kStatsStride = 4 + 2 * kStatsMaxK;  // doubles per state (layout i
 //   3 + m ||c^m||^2, 3 + K + m <c^m, cbar>.
 __host__ __device__ constexpr int kStatsSums(int K) { return 3 + 2 * K; }
 
-template <typename T, int V, int Q, bool EACH>
-__global__ __launch_bounds__(64 * kStatsMaxK) void k_replica_mean_stats(MeanParams p, double* __restrict__ partials) {
+// A 16-byte slot of a row as it is stored.
+template <typename T>
+struct Slot;
+template <>
+struct Slot<float> : f32x4 {};
+template <>
+struct Slot<uint16_t> : u16x8 {};
+__device__ __forceinline__ float widen(float a) { return a; }
+__device__ __forceinline__ float widen(uint16_t a) { return bf16_to_f32(a); }
+
+template <typename T, int V, int Q, bool EACH, bool O>
+__global__ __launch_bounds__(64 * kStatsMaxK) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 2 && O ? 7 : 8)))
+void k_replica_mean_stats(MeanParams p, double* __restrict__ partials) {
   constexpr int E = 64 * V;
   extern __shared__ __align__(16) float stage[];  // [2][K][64 V]
   __shared__ double red[kStatsMaxK][5];
@@ -1659,83 +1675,102 @@ __global__ __launch_bounds__(64 * kStatsMaxK) void k_replica_mean_stats(MeanPara
   const int32_t m = __builtin_amdgcn_readfirstlane((int32_t)(threadIdx.x >> 6));
   const int64_t block = launch_tile();
   if (block >= p.tiles) return;
-  const bool outer = (int32_t)blockIdx.z == p.outer_state && p.outer.xo != nullptr;
-  const double rk = 1.0 / (double)K;
+  const bool outer = O && (int32_t)blockIdx.z == p.outer_state;
+  const double rk = p.rk;
   T* row = reinterpret_cast<T*>(p.state[blockIdx.z]) + (int64_t)m * p.P;
   const uint32_t o = lane * V;
   double a_sq = 0.0, a_dot = 0.0, a_var = 0.0, a_mean = 0.0, a_ref = 0.0;
-  float a[V], nx[V] = {};
   auto first = [&](int i) { return (((block >> 3) * Q + i) * 8 + (block & 7)) * E; };
-  auto fetch = [&](int64_t e0, float (&to)[V]) {
-    const int32_t in_row = left_in_row(e0, p.P), n = in_row - (int32_t)o;
-    if (in_row >= E) load_n<true, T, V, true>(row + e0, o, n, to);
-    else load_n<false, T, V, true>(row + e0, o, n, to);
-  };
-  fetch(first(0), a);
-  for (int i = 0; i < Q; ++i) {
-    const int64_t e0 = first(i);
-    if (e0 >= p.P) break;  // uniform over the workgroup
-    const int32_t in_row = left_in_row(e0, p.P), n = in_row - (int32_t)o;
-    float* buf = stage + (i & 1) * K * E;
-    if (i + 1 < Q) fetch(first(i + 1), nx);
-    float xo[V];
-    if (outer) {
-      if (in_row >= E) load_n<true, float, V, false>(p.outer.xo + e0, o, n, xo);
-      else load_n<false, float, V, false>(p.outer.xo + e0, o, n, xo);
-    }
-    lds_put<V>(buf + m * E + o, a);
-    __syncthreads();
-    average_stages<E>(buf, K, 1, in_row, rk, p.outer, false, OuterAhead<1>{}, e0);
-    __syncthreads();
-    float mean[V], out[V];
-    lds_get<V>(buf + o, mean);
-    if (outer) {
-      __syncthreads();  // every wave has read the means before the outer step rewrites them
-      if (p.outer.update)
-        for (int32_t j = threadIdx.x; j < E; j += blockDim.x)
-          if (j < in_row) buf[j] = outer_element(p.outer, e0 + j, p.outer.xo[e0 + j], p.outer.mom[e0 + j], buf[j]);
+  // all Q pieces whole: one branch for the workgroup, so that a piece waits
+  // for its own loads and leaves the next one's in flight
+  auto pieces = [&](auto full) {
+    constexpr bool F = decltype(full)::value;
+    auto fetch = [&](int64_t e0) {
+      const int32_t n = left_in_row(e0, p.P) - (int32_t)o;
+      typename Slot<T>::type a = {};  // a piece past the row is not loaded
+      if (F || n + (int32_t)o >= E) {
+        a = ld<true, Slot<T>>(at((const T*)row + e0, o));
+      } else if (e0 < p.P) {
+        T b[V];
+#pragma unroll
+        for (int t = 0; t < V; ++t) b[t] = *at((const T*)row + e0, o + min(t, n - 1));
+#pragma unroll
+        for (int t = 0; t < V; ++t) a[t] = t < n ? b[t] : (T)0;
+      }
+      return a;
+    };
+    typename Slot<T>::type cur = fetch(first(0)), next = cur;
+#pragma unroll 1
+    for (int i = 0; i < Q; ++i) {
+      const int64_t e0 = first(i);
+      if (!F && e0 >= p.P) break;  // uniform over the workgroup
+      const int32_t in_row = F ? E : left_in_row(e0, p.P), n = in_row - (int32_t)o;
+      const bool whole = F || in_row >= E;
+      float* buf = stage + (i & 1) * K * E;
+      if (i + 1 < Q) next = fetch(first(i + 1));
+      float a[V], xo[V];
+      if (outer) {
+        if (whole) load_n<true, float, V, false>(p.outer.xo + e0, o, n, xo);
+        else load_n<false, float, V, false>(p.outer.xo + e0, o, n, xo);
+      }
+#pragma unroll
+      for (int t = 0; t < V; ++t) a[t] = widen((T)cur[t]);
+      lds_put<V>(buf + m * E + o, a);
       __syncthreads();
-      lds_get<V>(buf + o, out);
-    } else {
+      average_stages<E>(buf, K, 1, in_row, rk, p.outer, false, OuterAhead<1>{}, e0);
+      __syncthreads();
+      float mean[V], out[V];
+      lds_get<V>(buf + o, mean);
+      if (outer) {
+        __syncthreads();  // every wave has read the means before the outer step rewrites them
+        if (p.outer.update)
+          for (int32_t j = threadIdx.x; j < E; j += blockDim.x)
+            if (j < in_row) buf[j] = outer_element(p.outer, e0 + j, p.outer.xo[e0 + j], p.outer.mom[e0 + j], buf[j]);
+        __syncthreads();
+        lds_get<V>(buf + o, out);
+      } else {
 #pragma unroll
-      for (int t = 0; t < V; ++t) out[t] = mean[t];
-    }
-    // store first, then reduce the diagnostics while the stores drain
-    if (in_row >= E) store_n<true, T, V, true>(row + e0, o, n, out);
-    else store_n<false, T, V, true>(row + e0, o, n, out);
-    // the terms of the piece's V elements (values, means and outer parameters
-    // beyond the row are 0): each product rounded to fp32 once, then added to
-    // the fp64 sums (EACH) or to an fp32 sum that joins them once per piece
-    float f_sq = 0.0f, f_dot = 0.0f, f_var = 0.0f, f_mean = 0.0f, f_ref = 0.0f;
-#pragma unroll
-    for (int t = 0; t < V; ++t) {
-      const float cbar = outer ? xo[t] - mean[t] : mean[t];
-      const float c = outer ? xo[t] - a[t] : a[t];
-      const float dv = a[t] - mean[t];  // c - cbar up to sign
-      auto add = [&](double& sum, float& part, float p, float q) {
-        if constexpr (EACH) sum += (double)(p * q);
-        else part = __builtin_fmaf(p, q, part);
-      };
-      add(a_sq, f_sq, c, c);
-      add(a_dot, f_dot, c, cbar);
-      add(a_var, f_var, dv, dv);
-      if (m == 0) {
-        add(a_mean, f_mean, cbar, cbar);
-        if (outer) add(a_ref, f_ref, xo[t], xo[t]);
+        for (int t = 0; t < V; ++t) out[t] = mean[t];
       }
-    }
-    if constexpr (!EACH) {
-      a_sq += (double)f_sq;
-      a_dot += (double)f_dot;
-      a_var += (double)f_var;
-      if (m == 0) {
-        a_mean += (double)f_mean;
-        if (outer) a_ref += (double)f_ref;
-      }
-    }
+      // store first, then reduce the diagnostics while the stores drain
+      if (whole) store_n<true, T, V, true>(row + e0, o, n, out);
+      else store_n<false, T, V, true>(row + e0, o, n, out);
+      // the terms of the piece's V elements (values, means and outer parameters
+      // beyond the row are 0): each product rounded to fp32 once, then added to
+      // the fp64 sums (EACH) or to an fp32 sum that joins them once per piece
+      float f_sq = 0.0f, f_dot = 0.0f, f_var = 0.0f, f_mean = 0.0f, f_ref = 0.0f;
 #pragma unroll
-    for (int t = 0; t < V; ++t) a[t] = nx[t];
-  }
+      for (int t = 0; t < V; ++t) {
+        const float c0 = widen((T)cur[t]);
+        const float cbar = outer ? xo[t] - mean[t] : mean[t];
+        const float c = outer ? xo[t] - c0 : c0;
+        const float dv = c0 - mean[t];  // c - cbar up to sign
+        auto add = [&](double& sum, float& part, float y, float z) {
+          if constexpr (EACH) sum += (double)(y * z);
+          else part = __builtin_fmaf(y, z, part);
+        };
+        add(a_sq, f_sq, c, c);
+        add(a_dot, f_dot, c, cbar);
+        add(a_var, f_var, dv, dv);
+        if (m == 0) {
+          add(a_mean, f_mean, cbar, cbar);
+          if (outer) add(a_ref, f_ref, xo[t], xo[t]);
+        }
+      }
+      if constexpr (!EACH) {
+        a_sq += (double)f_sq;
+        a_dot += (double)f_dot;
+        a_var += (double)f_var;
+        if (m == 0) {
+          a_mean += (double)f_mean;
+          if (outer) a_ref += (double)f_ref;
+        }
+      }
+      cur = next;
+    }
+  };
+  if (first(Q - 1) + E <= p.P) pieces(BoolC<true>{});
+  else pieces(BoolC<false>{});
   // the workgroup's sums, fixed order
   const double sq = wave_sum(a_sq), dot = wave_sum(a_dot), var = wave_sum(a_var);
   const double mn = wave_sum(a_mean), ref = wave_sum(a_ref);

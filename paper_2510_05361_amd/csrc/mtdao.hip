@@ -391,8 +391,12 @@ void launch_stats(MeanParams q, int nstates, double* partials, double* out, hipS
   q.tiles = nb;
   const size_t lds = (size_t)2 * q.K * 64 * V * sizeof(float);
   auto go = [&](auto kernel) { hipLaunchKernelGGL(kernel, tile_grid(nb, nstates), dim3(64 * q.K), lds, st, q, partials); };
-  if (q.P % V == 0) go(k_replica_mean_stats<T, V, kStatsPieces, false>);
-  else go(k_replica_mean_stats<T, V, kStatsPieces, true>);
+  auto with = [&](auto each) {
+    if (q.outer_state < 0) go(k_replica_mean_stats<T, V, kStatsPieces, decltype(each)::value, false>);
+    else go(k_replica_mean_stats<T, V, kStatsPieces, decltype(each)::value, true>);
+  };
+  if (q.P % V == 0) with(BoolC<false>{});
+  else with(BoolC<true>{});
   hipLaunchKernelGGL(k_stats_reduce, dim3((unsigned)nc, nstates), dim3(kStatsBlock), 0, st, partials, nb, ns);
   hipLaunchKernelGGL(k_stats_finalize, dim3(nstates), dim3(kStatsBlock), 0, st, partials, nb, q.K, out);
 }
@@ -882,6 +886,7 @@ int32_t run_sync_stats(mtdao_handle* h, uint32_t mask, uint32_t* applied_mask, d
   mp.P = c.numel;
   mp.K = c.replicas;
   mp.outer_state = -1;
+  mp.rk = 1.0 / (double)c.replicas;
   // under Nesterov the diagnostics of x are those of the pseudo-gradients
   // x_outer - x^m also when the outer step of this s has already run
   mp.outer = outer_params(h, claim_outer_step(h, m, h->s));

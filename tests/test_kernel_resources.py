@@ -66,16 +66,15 @@ def test_no_kernel_spills(rows):
     assert not spilling, spilling
 
 
-# The bf16 diagnostics kernel with 16-byte slots (8 elements per lane)
-# needs 68 registers: 7 waves per SIMD, which still holds three 8-wave
-# workgroups per CU (K = 8); held to 64 it spilled.
-EXEMPT = ("k_replica_mean_statsItLi8E",)
+# The diagnostics of bf16 parameters under the OuterOpt (8 elements per lane
+# with their outer parameters) need 70 registers: 7 waves per SIMD, which
+# hold three 8-wave workgroups per CU (K = 8); held to 64 they spilled.
+SEVEN_WAVES = ("k_replica_mean_statsItLi8ELi4ELb0ELb1E", "k_replica_mean_statsItLi8ELi4ELb1ELb1E")
 
 
 def test_wave_per_replica_kernels_keep_eight_waves(rows):
-    low = [(r["name"], r["Occupancy"]) for r in rows
-           if any(k in r["name"] for k in WAVE_KERNELS) and r["Occupancy"] < 8
-           and not any(x in r["name"] for x in EXEMPT)]
+    low = [(r["name"], r["Occupancy"]) for r in rows if any(k in r["name"] for k in WAVE_KERNELS)
+           and r["Occupancy"] < (7 if any(x in r["name"] for x in SEVEN_WAVES) else 8)]
     assert not low, low
     assert sum(any(k in r["name"] for k in WAVE_KERNELS) for r in rows) > 20
 
