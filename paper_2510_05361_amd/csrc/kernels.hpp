@@ -1539,9 +1539,12 @@ __device__ __forceinline__ double wave_sum(double a) {
 }
 
 // Partial sums of g^2 in fp64 for replica blockIdx.y; each block writes
-// one partial (fixed order: deterministic for a fixed grid).  A tile that
-// lies in the row issues its U loads back to back, so U vector loads per
-// lane are in flight; the last ones are read element by element.
+// one partial (fixed order: deterministic for a fixed grid).  A tile issues
+// its U loads back to back, so U vector loads per lane are in flight.  A
+// tile's pieces are spread over 8 T elements, so the last eight tiles of a
+// row, which are all tiles of a short one, reach past its end: there a lane
+// whose slot does loads the row's last V elements instead and counts those
+// that lie in its slot.
 template <typename GT, int V, int U, int C>
 __global__ __launch_bounds__(kBlock) void k_sumsq_partial(const void* gp, int64_t P, double* __restrict__ partials) {
   constexpr int T = kBlock * V * U;
@@ -1550,24 +1553,38 @@ __global__ __launch_bounds__(kBlock) void k_sumsq_partial(const void* gp, int64_
   const int32_t in_row = left_in_row(base, P);
   const uint32_t last = (uint32_t)tile_elem<T, C>(0, ((U - 1) * kBlock + (kBlock - 1)) * V) + V;
   double acc = 0.0;
+  auto offset = [](int k) { return (uint32_t)tile_elem<T, C>(0, (k * kBlock + (int)threadIdx.x) * V); };
   auto tile = [&](auto full) {
     constexpr bool F = decltype(full)::value;
     float a[U][V];
 #pragma unroll
     for (int k = 0; k < U; ++k) {
-      const uint32_t o = (uint32_t)tile_elem<T, C>(0, (k * kBlock + (int)threadIdx.x) * V);
-      load_n<F, GT, V, false>(g, o, in_row - (int32_t)o, a[k]);
+      const uint32_t o = offset(k), end = (uint32_t)in_row - V;
+      load_n<true, GT, V, false>(g, F || o < end ? o : end, V, a[k]);
     }
 #pragma unroll
-    for (int k = 0; k < U; ++k)
+    for (int k = 0; k < U; ++k) {
+      // elements [V - n, V) of the load lie in the slot
+      const int32_t n = F ? V : in_row - (int32_t)offset(k);
 #pragma unroll
       for (int t = 0; t < V; ++t) {
-        const double d = (double)a[k][t];  // 0 beyond the row
+        const double d = F || t >= V - n ? (double)a[k][t] : 0.0;
         acc = __builtin_fma(d, d, acc);
       }
+    }
   };
-  if (in_row >= (int32_t)last) tile(BoolC<true>{});
-  else tile(BoolC<false>{});
+  if (in_row >= (int32_t)last) {
+    tile(BoolC<true>{});
+  } else if (in_row >= V) {
+    tile(BoolC<false>{});
+  } else if (threadIdx.x == 0) {  // fewer elements than a slot
+    for (int32_t t = 0; t < in_row; ++t) {
+      float a[1];
+      load_v<GT, 1, false>(g, t, a);
+      const double d = (double)a[0];
+      acc = __builtin_fma(d, d, acc);
+    }
+  }
   acc = wave_sum(acc);
   __shared__ double ws[kBlock / 64];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;

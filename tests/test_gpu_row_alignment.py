@@ -83,3 +83,23 @@ def test_ragged_diagnostics_sum_each_product_in_fp64(dtype, P):
     for m in range(K):
         assert stats[abi.MTDAO_STAT_WORKER_SQ + m] == want and stats[abi.MTDAO_STAT_WORKER_DOT + m] == want
     opt.close()
+
+
+@pytest.mark.parametrize("g", ["f32", "bf16"])
+@pytest.mark.parametrize("P", [1, 3, 4, 5, 255, 256, 2049, 8191, 65_535, 65_536, 65_539, 131_075])
+def test_clip_norm_of_row_ends(P, g):
+    """The norm pass at the end of a row: fewer elements than a slot, a
+    partial slot, rows shorter than a tile's span (65,536 elements) and just
+    above it.  Integer gradients make every norm exact, and from x = 0 one
+    step with beta = 0, omega = 1, lr = 1 leaves x = -scale g, one rounding."""
+    K, rho = 3, 2.0
+    cfg = abi.make_config("sgdm", K, (0.0,), (1.0,), P, clip_rho=rho, grad_dtype=g)
+    log(f"case norm {g} P={P}")
+    opt = MtdaoOptimizer(cfg, torch.device("cuda"), x0=torch.zeros(P, device="cuda"))
+    gen = torch.Generator(device="cuda").manual_seed(P)
+    grad = torch.randint(-16, 17, (K, P), device="cuda", generator=gen).float()
+    grad[:, -1] = 16.0  # a norm of more than rho, and a last element that counts
+    opt.step(grad.to(torch.bfloat16) if g == "bf16" else grad, 1.0)
+    scale = (rho / grad.double().square().sum(1).sqrt()).float()
+    assert torch.equal(opt.x, -(scale[:, None] * grad))
+    opt.close()
