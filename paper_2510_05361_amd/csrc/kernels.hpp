@@ -1412,9 +1412,9 @@ struct MeanParams {
 
 // E_m[S] for the state blockIdx.z: every element becomes
 // S^0 + (sum_{m>=1} (S^m - S^0)) / K (mean_of) and is stored to all K rows.
-// Each thread reads the K rows of its own columns and writes them back, so
-// the in-place update has no cross-thread hazard.
-template <typename T, int V, bool NT>
+// Each thread reads the K rows of its own columns, R at a time, and writes
+// them back, so the in-place update has no cross-thread hazard.
+template <typename T, int V, bool NT, int R>
 __global__ __launch_bounds__(kBlock) void k_replica_mean(MeanParams p) {
   T* s = reinterpret_cast<T*>(p.state[blockIdx.z]);
   const double rk = 1.0 / (double)p.K;
@@ -1431,14 +1431,13 @@ __global__ __launch_bounds__(kBlock) void k_replica_mean(MeanParams p) {
     load_n<F, T, V, NT>(s + base, o, n, s0);
 #pragma unroll
     for (int t = 0; t < V; ++t) d[t] = 0.0;
-    // four rows' loads in flight
     int32_t m = 1;
-    for (; m + 4 <= p.K; m += 4) {
-      float r[4][V];
+    for (; m + R <= p.K; m += R) {
+      float r[R][V];
 #pragma unroll
-      for (int i = 0; i < 4; ++i) load_n<F, T, V, NT>(s + (int64_t)(m + i) * p.P + base, o, n, r[i]);
+      for (int i = 0; i < R; ++i) load_n<F, T, V, NT>(s + (int64_t)(m + i) * p.P + base, o, n, r[i]);
 #pragma unroll
-      for (int i = 0; i < 4; ++i)
+      for (int i = 0; i < R; ++i)
 #pragma unroll
         for (int t = 0; t < V; ++t) mean_add(d[t], r[i][t], s0[t]);
     }

@@ -56,6 +56,36 @@ def test_every_state_staged(K):
     _check(_workload("adam", 1027, K, steps=12), f"staged-{K}")
 
 
+@pytest.mark.parametrize("K", [17, 32])
+@pytest.mark.parametrize("x,P", [("f32", 1024 * 300 + 5), ("f32", 4_300_003), ("bf16", 2048 * 300 + 9),
+                                 ("bf16", 2_200_006), ("bf16", 513)])
+def test_mean_of_many_replicas(x, P, K):
+    """K > 16, launches below and above four workgroups per CU, with a last
+    piece of fewer elements than a slot and of more.  The product with 1 / 32
+    is exact, so the fp64 mean formed here is the kernel's bit for bit; 1 / 17
+    is not, and the product's own fp64 rounding, which the kernel's fma does
+    not have, breaks the ties of the final rounding: one ulp apart at most, or
+    2^-48 where the mean vanishes (values and differences are below 16, so
+    each of the two fp64 roundings here is at most 2^-50)."""
+    cfg = abi.make_config("sgdm", K, (0.9,), (0.9,), P, param_dtype=x, grad_dtype=x)
+    log(f"case mean {x} P={P} K={K}")
+    opt = MtdaoOptimizer(cfg, torch.device("cuda"), x0=torch.zeros(P, device="cuda"))
+    opt.x.normal_(0.0, 1.0, generator=torch.Generator(device="cuda").manual_seed(P))
+    before = opt.x.clone()
+    assert opt.sync(1) == 1
+    d = torch.zeros(P, dtype=torch.float64, device="cuda")
+    for m in range(1, K):
+        d += before[m].double() - before[0].double()
+    want = (before[0].double() + d * (1.0 / K)).float().to(opt.x.dtype)
+    assert torch.equal(opt.x, opt.x[:1].expand_as(opt.x))
+    if K == 32:
+        assert torch.equal(opt.x[0], want)
+    else:
+        assert torch.allclose(opt.x[0].float(), want.float(), rtol=2.0 ** (-7 if x == "bf16" else -23),
+                              atol=2.0 ** -48)
+    opt.close()
+
+
 @pytest.mark.parametrize("form,K,P,x", [("adam", 3, 1_500_003, "f32"), ("sgdm", 8, 1_000_005, "bf16")])
 def test_limited_residency(form, K, P, x):
     """More than 64 MB loaded per launch."""
