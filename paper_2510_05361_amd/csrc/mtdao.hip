@@ -264,7 +264,14 @@ void launch_step(const mtdao_config& c, StepParams p, hipStream_t st) {
     p.n = p.P * c.replicas;
     p.rp = 1.0 / (double)p.P;
     const dim3 grid = tile_grid(tiles_for<B * V, piece_for(V)>(p.n));
-    const size_t lds = p.n * L.bytes >= kResidentMin ? resident_lds(L.resident) : 0;
+    // the clip norm leaves gradients of up to about twice the 256 MB MALL
+    // partly there; a step that loads little else then runs faster with every
+    // wave that the CUs hold (SGDM N = 1 K = 4 fp32, 256 MiB of gradients 242.6
+    // us limited, 233.7 us not, in bf16 318.9 / 304.4 us; 960 MB 877 / 885 us;
+    // N = 2 fp32 314.6 / 315.2 us; Adam N = 1 in bf16 588 / 612 us)
+    constexpr bool kFew = FORM == kSgdm && N == 1;
+    const bool cached = kFew && p.scale != nullptr && p.n * (int64_t)sizeof(GT) <= (INT64_C(512) << 20);
+    const size_t lds = p.n * L.bytes >= kResidentMin && !cached ? resident_lds(L.resident) : 0;
     auto go = [&](auto kernel) { hipLaunchKernelGGL(kernel, grid, dim3(B), lds, st, p); };
     if constexpr (FORM == kAdopt) {
       if (c.adopt_order == MTDAO_ADOPT_CUR) go(k_local_step<FORM, N, XT, GT, V, kStepNT, kCur, kNoScale, B>);
