@@ -340,19 +340,35 @@ inline dim3 group_grid(int64_t pieces, int32_t group, int32_t nz = 1) {
 constexpr int64_t kResidentMin = INT64_C(64) << 20;
 constexpr size_t resident_lds(int n) { return (size_t)(128 / n > 51 ? 51 : 128 / n) * 1280; }
 
-// Workgroups per CU of the fused step with one wave per replica, for `bytes`
-// loaded per element.  Its barriers ask for more bytes in flight than the
-// plain step, and the fewer streams a form has the more waves those take: 12
-// waves for six 4-byte streams (72 KiB of loads), 28 for two (56 KiB).  At
-// least two workgroups, which K > 8 has by its size (one took 0.86 to 0.96 of
-// the rate), unless their LDS does not allow it (more than 80 KiB each: six
-// due states of 14 or more rows).  All due, 1.6 GB loaded, same buffers of an
-// MI355X, unlimited / as here: SGDM N = 1 K = 4 457 / 428 us (12 waves for
-// every form took 474), in bf16 K = 2 439 / 438 us (687) and K = 6
-// 479 / 491 us (676), Adam N = 1 K = 4 499 / 457 us (484), Adam N = 2 K = 4
-// 500 / 472 us; Adam N = 3 354M x 4 11.39 / 10.54 ms.
-constexpr int wave_resident(int K, int bytes) {
-  const int waves = bytes <= 8 ? 28 : bytes <= 10 ? 24 : bytes <= 14 ? 18 : bytes <= 18 ? 16 : bytes <= 22 ? 14 : 12;
+// Workgroups per CU of the steps with one wave per replica, for `bytes`
+// loaded per element.  Their barriers ask for more bytes in flight than the
+// plain step, and the fewer streams a form has the more waves those take:
+// from no limit at two 2-byte and one 4-byte stream (8 bytes) to 12 waves at
+// six 4-byte ones (72 KiB of loads).  More also where every state is due
+// (`many`: more than half; all stores wait for the exchange), where x takes
+// the OuterOpt (`outer`, whose parameters are loaded with the tile) and where the
+// clip norm has just left the gradients in the MALL (`clip`).  At least two
+// workgroups, which K > 8 has by its size (one took 0.86 to 0.96 of the rate),
+// unless their LDS does not allow it (more than 80 KiB each: six due states
+// of 14 or more rows).  The table is the best of 2, 3, 4, 5, 6, 8, 10 and 14
+// workgroups and no limit over K = 2, 3, 4, 5, 6, 8, seven forms, x or all
+// states due, with clipping and without, 0.3 and 1.2 GB loaded, same buffers
+// of an MI355X: within 1 % of each row's best on average, where one value per
+// form was 1 to 4 % off and with clipping up to 17 % (SGDM N = 1 fp32 K = 4
+// all due, clipped, 1.2 GB: 400 us at 18 waves, 348 us at 28; Adam N = 1
+// K = 4 408 us at 16, 349 us at 24).  Under the OuterOpt the waves are rounded
+// up to a whole workgroup (Adam N = 1 K = 7, 1.2 GB: two 398 us, three 347 us;
+// N = 2 K = 6 386 / 361 us).  12 waves against no limit: Adam N = 3 354M x 4
+// 10.54 against 11.39 ms.
+constexpr int wave_resident(int K, int bytes, bool many = false, bool clip = false, bool outer = false) {
+  int waves = 12;
+  if (bytes <= 8) waves = 32;
+  else if (bytes <= 10) waves = many && clip ? 28 : 24;
+  else if (bytes <= 14) waves = many ? (clip ? 28 : 24) : clip ? 24 : outer ? 20 : 18;
+  else if (bytes <= 18) waves = many ? (clip ? 24 : 18) : clip ? 21 : outer ? 18 : 16;
+  else if (bytes <= 22) waves = clip ? (many ? 18 : 16) : 14;
+  else if (many && clip) waves = 16;
+  if (outer && waves < 32) waves += K - 1;
   return waves / K > 2 ? waves / K : 2;
 }
 
@@ -1301,9 +1317,12 @@ void k_sgdm_averaged_momenta_waves(StepParams p0, uint32_t mask, int32_t K) {
   else piece(BoolC<false>{});
 }
 
-// The same with one exchange per due state, for K > 8 and row lengths that
-// are a multiple of V, as in k_local_step_sync_waves_rounds (16.8M x 16,
-// N = 2, all due: 1349 us, staged together 1371 us).
+// The same with one exchange per due state, for row lengths that are a
+// multiple of V and K > 8, as in k_local_step_sync_waves_rounds (16.8M x 16,
+// N = 2, all due: 1349 us, staged together 1371 us), or K > 4 and 8 bytes
+// loaded per element (N = 1, bf16 parameters and gradients, 1.2 GB loaded:
+// K = 5 341 us, staged together 360 us; K = 7 353 / 365 us, clipped 387 /
+// 406 us; K = 8 equal).
 template <int N, typename XT, typename GT, int V, int NTM>
 __global__ __launch_bounds__(64 * kWaveMaxK) __attribute__((amdgpu_waves_per_eu(8)))
 void k_sgdm_averaged_momenta_waves_rounds(StepParams p0, uint32_t mask, int32_t K) {

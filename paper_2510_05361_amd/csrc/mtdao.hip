@@ -244,10 +244,13 @@ void dispatch_step(const mtdao_config& c, F&& f) {
 constexpr int kStepV = 4;
 
 // LDS of a wave-per-replica step: `stages` of K pieces of 64 kStepV floats,
-// and enough that a CU holds wave_resident(K) workgroups.
-size_t wave_lds(int stages, int K, int bytes, int64_t P) {
+// and enough that a CU holds wave_resident workgroups (`mask`: the states
+// averaged, of `states`).
+size_t wave_lds(int stages, uint32_t mask, int states, const StepParams& p, int K, int bytes) {
   const size_t need = (size_t)stages * K * 64 * kStepV * sizeof(float);
-  return P * K * bytes >= kResidentMin ? std::max(need, resident_lds(wave_resident(K, bytes))) : need;
+  if (p.P * K * bytes < kResidentMin) return need;
+  const bool many = 2 * __builtin_popcount(mask) > states, outer = (mask & 1u) && p.outer.xo != nullptr;
+  return std::max(need, resident_lds(wave_resident(K, bytes, many, p.scale != nullptr, outer)));
 }
 
 // The local step alone, over the K P elements of every buffer as flat
@@ -309,7 +312,7 @@ void launch_step_sync(const mtdao_config& c, StepParams p, uint32_t mask, hipStr
       }
       p.group = row_group(p.P, sizeof(float));
       const dim3 grid = group_grid(pieces, p.group);
-      const size_t lds = wave_lds(__builtin_popcount(mask), K, kLoad, p.P);
+      const size_t lds = wave_lds(__builtin_popcount(mask), mask, 1 + N + (FORM != kSgdm ? 1 : 0), p, K, kLoad);
       auto go = [&](auto kernel) { hipLaunchKernelGGL(kernel, grid, block, lds, st, p, mask, K); };
       if constexpr (FORM == kAdopt) {
         if (c.adopt_order == MTDAO_ADOPT_CUR) {
@@ -321,7 +324,10 @@ void launch_step_sync(const mtdao_config& c, StepParams p, uint32_t mask, hipStr
       return;
     }
     const dim3 grid = tile_grid(tiles_for<kBlock * V, piece_for(V)>(p.P));
-    auto go = [&](auto kernel) { hipLaunchKernelGGL(kernel, grid, dim3(kBlock), 0, st, p, mask, K); };
+    // at most four workgroups per CU (K = 24, 4M, bf16, x due, SGDM N = 1
+    // 254 us with all that the registers allow, 244 us; Adam N = 1 415 / 405 us)
+    const size_t lds = p.P * K * kLoad >= kResidentMin ? resident_lds(4) : 0;
+    auto go = [&](auto kernel) { hipLaunchKernelGGL(kernel, grid, dim3(kBlock), lds, st, p, mask, K); };
     if constexpr (FORM == kAdopt) {
       if (c.adopt_order == MTDAO_ADOPT_CUR) {
         go(k_local_step_sync<FORM, N, XT, GT, V, kStepNT, kCur>);
@@ -453,7 +459,7 @@ void launch_sgdm_averaged_momenta(const mtdao_config& c, StepParams p, uint32_t 
       if (K > 1 && K <= kWaveMaxK) {
         // one wavefront per replica, one pass
         const int stages = std::max(1, __builtin_popcount(mask >> 1));
-        if (K > 8 && p.P % V == 0) {
+        if (K > (kLoad <= 8 ? 4 : 8) && p.P % V == 0) {
           hipLaunchKernelGGL((k_sgdm_averaged_momenta_waves_rounds<N, XT, GT, V, kStepNT>),
                              tile_grid((p.P + 64 * V - 1) / (64 * V)), dim3(64 * K), 0, st, p, mask, K);
           return;
@@ -461,7 +467,7 @@ void launch_sgdm_averaged_momenta(const mtdao_config& c, StepParams p, uint32_t 
         p.group = row_group(p.P, sizeof(float));
         hipLaunchKernelGGL((k_sgdm_averaged_momenta_waves<N, XT, GT, V, kStepNT>),
                            group_grid((p.P + 64 * V - 1) / (64 * V), p.group), dim3(64 * K),
-                           wave_lds(stages, K, kLoad, p.P), st, p, mask, K);
+                           wave_lds(stages, mask, 1 + N, p, K, kLoad), st, p, mask, K);
         return;
       }
       hipLaunchKernelGGL((k_sgdm_averaged_momenta<N, XT, GT, V, kStepNT>),

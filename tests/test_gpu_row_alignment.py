@@ -56,6 +56,14 @@ def test_every_state_staged(K):
     _check(_workload("adam", 1027, K, steps=12), f"staged-{K}")
 
 
+@pytest.mark.parametrize("form,K,P,x", [("sgdm", 4, 2_500_003, "f32"), ("sgdm", 5, 3_000_004, "bf16"),
+                                        ("adam", 2, 4_200_004, "f32")])
+def test_limits_by_due_states_and_clipping(form, K, P, x):
+    """Fused steps of more than 64 MB with clipping, x due, the moments due
+    and every state due: each takes its own limit of workgroups per CU."""
+    _check(_workload(form, P, K, x, x, steps=4), f"limits-{form}-{K}-{P}", run_oracle_parallel)
+
+
 @pytest.mark.parametrize("K", [17, 32])
 @pytest.mark.parametrize("x,P", [("f32", 1024 * 300 + 5), ("f32", 4_300_003), ("bf16", 2048 * 300 + 9),
                                  ("bf16", 2_200_006), ("bf16", 513)])

@@ -22,8 +22,11 @@ int main(int argc, char** argv) {
   long long tiles;
   int group;
   if (argc > 1) {  // "resident": replicas, bytes loaded per element; "group": row length, bytes of an element
+    const bool many = argc > 2 && argv[2][0] == '1', clip = argc > 3 && argv[3][0] == '1';
+    const bool outer = argc > 4 && argv[4][0] == '1';
     while (scanf("%lld %d", &tiles, &group) == 2)
-      printf("%d\n", argv[1][0] == 'r' ? mtdao::wave_resident((int)tiles, group) : mtdao::row_group(tiles, group));
+      printf("%d\n", argv[1][0] == 'r' ? mtdao::wave_resident((int)tiles, group, many, clip, outer)
+                                       : mtdao::row_group(tiles, group));
     return 0;
   }
   while (scanf("%lld %d", &tiles, &group) == 2) {
@@ -71,6 +74,18 @@ def test_grid_covers_the_tiles_and_little_more(grids, tiles, group):
     assert x * y >= whole
     # x a multiple of 16 keeps a tile's XCD and parity; at most that rounding is empty
     assert (y == 1 and x == whole) or (x % 16 == 0 and x * y - whole < 17 * y)
+
+
+@pytest.mark.parametrize("many", ["0", "1"])
+@pytest.mark.parametrize("clip", ["0", "1"])
+@pytest.mark.parametrize("outer", ["0", "1"])
+def test_more_due_states_and_clipping_never_lower_the_limit(program, many, clip, outer):
+    """Exchanging more states, reading gradients that the clip norm has just
+    read, or the OuterOpt asks for as many workgroups per CU or more."""
+    forms = [(k, b) for k in range(2, 17) for b in range(8, 29, 2)]
+    base, here = program(forms, "resident"), program(forms, "resident", many, clip, outer)
+    low = {f: (base[f], here[f]) for f in forms if here[f] < base[f] or here[f][0] < 2}
+    assert not low, low
 
 
 def test_fused_step_keeps_loads_in_flight(program):
