@@ -414,7 +414,13 @@ void launch_stats(MeanParams q, int nstates, double* partials, double* out, hipS
   const int64_t nb = stats_blocks(q.P, V), nc = (nb + kStatsChunk - 1) / kStatsChunk;
   const int32_t ns = kStatsSums(q.K);
   q.tiles = nb;
-  const size_t lds = (size_t)2 * q.K * 64 * V * sizeof(float);
+  // 24 waves per CU where more than 64 MB are loaded (the kernel's own 640 B of
+  // LDS count): one state 1.31B x 4 fp32 6.92 ms unlimited, 6.56 ms; 175M x 8
+  // bf16 1057 -> 1026 us; 700M x 2 bf16 1168 -> 1058 us.  From nine replicas on
+  // a CU holds two or three workgroups as it is.
+  const size_t need = (size_t)2 * q.K * 64 * V * sizeof(float);
+  const bool limit = q.K <= 8 && q.P * q.K * nstates * (int64_t)sizeof(T) >= kResidentMin;
+  const size_t lds = limit ? std::max(need, resident_lds(24 / q.K) - 640) : need;
   auto go = [&](auto kernel) { hipLaunchKernelGGL(kernel, tile_grid(nb, nstates), dim3(64 * q.K), lds, st, q, partials); };
   auto with = [&](auto each) {
     if (q.outer_state < 0) go(k_replica_mean_stats<T, V, kStatsPieces, decltype(each)::value, false>);
