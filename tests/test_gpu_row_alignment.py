@@ -51,9 +51,20 @@ def test_row_lengths(form, K, x, g, P):
 
 @pytest.mark.parametrize("K", [12, 16])
 def test_every_state_staged(K):
-    """Five due states of 12 and 16 replicas exchanged at once (s = 12): the
-    largest LDS request of the suite's forms, 80 KiB."""
+    """Five due states of 12 and 16 replicas exchanged at once (s = 12): an
+    LDS request of 80 KiB."""
     _check(_workload("adam", 1027, K, steps=12), f"staged-{K}")
+
+
+@pytest.mark.parametrize("K", [14, 16])
+@pytest.mark.parametrize("form", ["adam", "adopt"])
+def test_six_states_staged(form, K):
+    """x, four moments and v of 14 and 16 replicas exchanged at once (s = 12):
+    the largest LDS request that the dispatch can make, 96 KiB, which leaves a
+    CU one workgroup."""
+    w = _workload(form, 1027, K, steps=12).replace(beta1=(0.0, 0.5, 0.9, 0.999), omega=(0.1, 0.2, 0.3, 0.4),
+                                                   period_u=(4,) * 4)
+    _check(w, f"staged-n4-{form}-{K}")
 
 
 @pytest.mark.parametrize("form,K,P,x", [("sgdm", 4, 2_500_003, "f32"), ("sgdm", 5, 3_000_004, "bf16"),
@@ -100,15 +111,15 @@ def test_limited_residency(form, K, P, x):
     _check(_workload(form, P, K, x, x, steps=4), f"resident-{form}-{K}-{P}", run_oracle_parallel)
 
 
-@pytest.mark.parametrize("dtype,P", [("f32", 1027), ("f32", 262_145), ("bf16", 1028), ("bf16", 1031),
-                                     ("bf16", 262_145)])
-def test_ragged_diagnostics_sum_each_product_in_fp64(dtype, P):
+@pytest.mark.parametrize("dtype,P,K", [("f32", 1027, 4), ("f32", 262_145, 4), ("bf16", 1028, 4), ("bf16", 1031, 4),
+                                       ("bf16", 262_145, 4), ("bf16", 1031, 16)])
+def test_ragged_diagnostics_sum_each_product_in_fp64(dtype, P, K):
     """Rows that are no whole number of 16-byte slots add every product to
     the fp64 sums by itself.  Identical workers with the values 4096, 1, 1, 1
     in turn: each product (2^24 or 1) and every fp64 sum of them (integers
     below 2^53) is exact, so the diagnostics must be the integers themselves,
-    while an fp32 sum of a slot would lose every 1 beside a 2^24."""
-    K = 4
+    while an fp32 sum of a slot would lose every 1 beside a 2^24.  (K = 16 in
+    bf16: the largest LDS request of the diagnostics, 64 KiB.)"""
     cfg = abi.make_config("sgdm", K, (0.9,), (0.9,), P, param_dtype=dtype, grad_dtype=dtype)
     row = torch.ones(P, device="cuda")
     row[::4] = 4096.0
