@@ -356,19 +356,19 @@ constexpr size_t resident_lds(int n) { return (size_t)(128 / n > 51 ? 51 : 128 /
 // of an MI355X: within 1 % of each row's best on average, where one value per
 // form was 1 to 4 % off and with clipping up to 17 % (SGDM N = 1 fp32 K = 4
 // all due, clipped, 1.2 GB: 400 us at 18 waves, 348 us at 28; Adam N = 1
-// K = 4 408 us at 16, 349 us at 24).  Under the OuterOpt the waves are rounded
-// up to a whole workgroup (Adam N = 1 K = 7, 1.2 GB: two 398 us, three 347 us;
+// K = 4 408 us at 16, 349 us at 24).  Under the OuterOpt and K > 4 the waves are
+// rounded up to a whole workgroup (Adam N = 1 K = 7, 1.2 GB: two 398 us, three 347 us;
 // N = 2 K = 6 386 / 361 us).  12 waves against no limit: Adam N = 3 354M x 4
 // 10.54 against 11.39 ms.
 constexpr int wave_resident(int K, int bytes, bool many = false, bool clip = false, bool outer = false) {
   int waves = 12;
   if (bytes <= 8) waves = 32;
   else if (bytes <= 10) waves = many && clip ? 28 : 24;
-  else if (bytes <= 14) waves = many ? (clip ? 28 : 24) : clip ? 24 : outer ? 20 : 18;
-  else if (bytes <= 18) waves = many ? (clip ? 24 : 18) : clip ? 21 : outer ? 18 : 16;
-  else if (bytes <= 22) waves = clip ? (many ? 18 : 16) : 14;
+  else if (bytes <= 14) waves = many ? (clip ? 28 : 24) : clip ? 24 : outer ? 21 : 18;
+  else if (bytes <= 16) waves = many ? (clip ? 24 : 18) : clip ? 21 : outer ? 18 : 16;
+  else if (bytes <= 22) waves = many && clip ? 18 : 14;
   else if (many && clip) waves = 16;
-  if (outer && waves < 32) waves += K - 1;
+  if (outer && K > 4 && waves < 32) waves += K - 1;
   return waves / K > 2 ? waves / K : 2;
 }
 

@@ -5,7 +5,7 @@
  * compared with the CPU oracle (oracle/_liboracle.so, test infrastructure)
  * run on the same inputs:
  *   case 1: Adam form (Algorithm 1), N = 3, K = 4 workers, P = 10007 (a
- *           row length that is not a multiple of 4: the scalar path), with
+ *           row length that is not a multiple of 4: unaligned rows), with
  *           every averaging event folded into mtdao_step_sync;
  *   case 2: SGDM form (Algorithm 3), N = 2, K = 5, P = 8204, per-worker
  *           global-norm clip rho = 0.05 (active), mtdao_local_step followed

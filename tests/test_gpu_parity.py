@@ -34,7 +34,7 @@ def _steps(w, start=0):
 def _aligned_tail(name: str, target: int, tail: int) -> int:
     """A tail of at least ``tail`` elements that makes the row length a
     multiple of 8 (16-byte slots for fp32 and bf16 rows) when ``tail`` is
-    even, and odd (the one-element path) when ``tail`` is odd."""
+    even, and odd (rows that start off the vector grid) when ``tail`` is odd."""
     base = synth.small_variant(synth.WORKLOADS[name], target).numel
     if tail % 2:
         return tail + (base + tail + 1) % 2
@@ -46,7 +46,7 @@ def _aligned_tail(name: str, target: int, tail: int) -> int:
 def test_small_variant_full_compare(name, tail):
     """~60k elements per replica (tens of tiles) plus a ragged tail; the
     aligned tail makes the row length a multiple of 8 (the 16-byte slots of
-    every kernel), the odd tail takes the one-element path."""
+    every kernel), the odd tail makes rows start off the vector grid."""
     w = synth.small_variant(synth.WORKLOADS[name], 60_000, tail=_aligned_tail(name, 60_000, tail))
     assert w.numel % 8 == 0 if tail % 2 == 0 else w.numel % 2 == 1
     log(f"case small {w.name} P={w.numel} K={w.replicas} T={w.steps}")
@@ -97,7 +97,7 @@ def test_full_size_every_element_written(name):
     """Write coverage of the full-size launches, on every element of every
     replica: SGDM with N = 1, beta = 0, omega = 1, lr = 1 and no clip makes
     one update u = g and x = x0 - g exactly (one fp32 rounding, as torch's
-    subtraction), so the plain step (tile placement, replica-pair windows)
+    subtraction), so the plain step (tile placement, flat buffers)
     must leave exactly those values; then the standalone mean of x and u
     and a fused step with x and u due must leave every row equal to
     S^0 + (sum_{m>=1} (S^m - S^0)) / K formed in fp64 in replica order and
@@ -747,7 +747,7 @@ def test_sync_stats_against_oracle(name, outer, tail):
     diagnostics of every averaged state equal the oracle's on the same
     pre-average values (fp32: 1e-5 relative; bf16 x: rounding flips of x
     shift the worker differences by a bf16 ulp, bound 2e-3).  An odd tail
-    takes the one-element-per-lane path."""
+    makes rows that are no whole number of slots."""
     w = _stats_case(name, tail=tail)
     w = w.replace(period_x=4, period_u=(6,) * w.n_moments, period_v=8, steps=24)
     log(f"case stats {w.name} K={w.replicas} outer={outer}")
@@ -1062,9 +1062,9 @@ def test_power_of_two_gradient_scale_invariance(name, k, fused):
 def test_identical_workers_equal_one_worker(name):
     """K workers that all receive worker 0's gradient follow, bit for bit,
     the trajectory of a single worker: averaging identical rows is an exact
-    no-op, the clip norms agree, and the K = 1 launch shapes (half-row
-    windows, no averaging) compute the same per-element arithmetic as the
-    replica-pair windows and the averaging kernels.  No oracle is involved."""
+    no-op, the clip norms agree, and the K = 1 launches (no averaging) compute the
+    same per-element arithmetic as those of six rows and the averaging
+    kernels.  No oracle is involved."""
     w = synth.small_variant(synth.WORKLOADS[name], 30_000, tail=37)
     w = w.replace(replicas=6, steps=20, period_x=3, period_u=(4,) * w.n_moments, period_v=5)
     log(f"case identical workers {w.name}")
