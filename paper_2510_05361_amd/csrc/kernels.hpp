@@ -314,12 +314,14 @@ inline dim3 tile_grid(int64_t tiles, int32_t nz = 1) {
 // K = 4, x due, 30M + 1 927 -> 858 us, 30M + 8 895 -> 841 us, 30M + 16
 // 806 -> 794 us, 30M + 32 (whole lines) 749 -> 774 us; mean K = 4, bf16,
 // 80M + 32 243 -> 225 us, fp32, 40M + 4 227 -> 209 us; K = 16, fp32, 40M + 32
-// (whole lines) 888 -> 926 us.  Groups of 16 and 32 were equal to 8.  Pieces
-// past the row have no elements.
+// (whole lines) 888 -> 926 us.  Groups of 16 and 32 were equal to 8.  (The
+// piece formed by shifts starts a workgroup's loads earlier and was slower:
+// 98M x 3 1936 -> 2017 us, 25M x 3 484 -> 500 us.)  Pieces past the row have
+// no elements.
 __device__ __forceinline__ int64_t group_piece(int32_t group) {
   const int64_t t = launch_tile();
   if (group == 1) return t;
-  return (t & ~(int64_t)63) | ((t & 7) << 3) | ((t >> 3) & 7);
+  return t / (8 * group) * (8 * group) + (t & 7) * group + (t >> 3) % group;
 }
 inline int32_t row_group(int64_t P, int bytes) { return P * bytes % 128 == 0 ? 1 : 8; }
 inline dim3 group_grid(int64_t pieces, int32_t group, int32_t nz = 1) {
@@ -354,7 +356,8 @@ constexpr size_t resident_lds(int n) { return (size_t)(128 / n > 51 ? 51 : 128 /
 // workgroups and no limit over K = 2, 3, 4, 5, 6, 8, seven forms, x or all
 // states due, with clipping and without, 0.3 and 1.2 GB loaded, same buffers
 // of an MI355X: within 1 % of each row's best on average, where one value per
-// form was 1 to 4 % off and with clipping up to 17 % (SGDM N = 1 fp32 K = 4
+// form was 1 to 4 % off and with clipping up to 17 % (16 bytes, all due, K = 6:
+// three workgroups 361 us, two 347 us, K = 3 six 346 us, no limit 352 us; SGDM N = 1 fp32 K = 4
 // all due, clipped, 1.2 GB: 400 us at 18 waves, 348 us at 28; Adam N = 1
 // K = 4 408 us at 16, 349 us at 24).  Under the OuterOpt and K > 4 the waves are
 // rounded up to a whole workgroup (Adam N = 1 K = 7, 1.2 GB: two 398 us, three 347 us;
@@ -365,7 +368,7 @@ constexpr int wave_resident(int K, int bytes, bool many = false, bool clip = fal
   if (bytes <= 8) waves = 32;
   else if (bytes <= 10) waves = many && clip ? 28 : 24;
   else if (bytes <= 14) waves = many ? (clip ? 28 : 24) : clip ? 24 : outer ? 21 : 18;
-  else if (bytes <= 16) waves = many ? (clip ? 24 : 18) : clip ? 21 : outer ? 18 : 16;
+  else if (bytes <= 16) waves = many ? (clip ? 24 : K > 5 ? 12 : 18) : clip ? 21 : outer ? 18 : 16;
   else if (bytes <= 22) waves = many && clip ? 18 : 14;
   else if (many && clip) waves = 16;
   if (outer && K > 4 && waves < 32) waves += K - 1;
