@@ -348,21 +348,22 @@ constexpr size_t resident_lds(int n) { return (size_t)(128 / n > 51 ? 51 : 128 /
 // from no limit at two 2-byte and one 4-byte stream (8 bytes) to 12 waves at
 // six 4-byte ones (72 KiB of loads).  More also where every state is due
 // (`many`: more than half; all stores wait for the exchange), where x takes
-// the OuterOpt (`outer`, whose parameters are loaded with the tile) and where the
-// clip norm has just left the gradients in the MALL (`clip`).  At least two
-// workgroups, which K > 8 has by its size (one took 0.86 to 0.96 of the rate),
-// unless their LDS does not allow it (more than 80 KiB each: six due states
-// of 14 or more rows).  The table is the best of 2, 3, 4, 5, 6, 8, 10 and 14
-// workgroups and no limit over K = 2, 3, 4, 5, 6, 8, seven forms, x or all
-// states due, with clipping and without, 0.3 and 1.2 GB loaded, same buffers
-// of an MI355X: within 1 % of each row's best on average, where one value per
-// form was 1 to 4 % off and with clipping up to 17 % (16 bytes, all due, K = 6:
-// three workgroups 361 us, two 347 us, K = 3 six 346 us, no limit 352 us; SGDM N = 1 fp32 K = 4
-// all due, clipped, 1.2 GB: 400 us at 18 waves, 348 us at 28; Adam N = 1
-// K = 4 408 us at 16, 349 us at 24).  Under the OuterOpt and K > 4 the waves are
-// rounded up to a whole workgroup (Adam N = 1 K = 7, 1.2 GB: two 398 us, three 347 us;
-// N = 2 K = 6 386 / 361 us).  12 waves against no limit: Adam N = 3 354M x 4
-// 10.54 against 11.39 ms.
+// the OuterOpt (`outer`, whose parameters are loaded with the tile) and where
+// the clip norm has just left the gradients in the MALL (`clip`).  At least
+// two workgroups, which K > 8 has by its size (one took 0.86 to 0.96 of the
+// rate), unless their LDS does not allow it (more than 80 KiB each: six due
+// states of 14 or more rows).  The table is the best of 2, 3, 4, 5, 6, 8, 10
+// and 14 workgroups and no limit over K = 2, 3, 4, 5, 6, 8, seven forms, x or
+// all states due, with clipping and without, 0.3 and 1.2 GB loaded, same
+// buffers of an MI355X: within 1 % of each row's best on average, where one
+// value per form was 1 to 4 % off and with clipping up to 17 % (SGDM N = 1
+// fp32 K = 4 all due, clipped, 1.2 GB: 400 us at 18 waves, 348 us at 28; Adam
+// N = 1 K = 4 408 us at 16, 349 us at 24; without clipping SGDM N = 2 K = 6
+// three workgroups 361 us, two 347 us, K = 3 six 346 us, unlimited 352 us).
+// Under the OuterOpt and K > 4 the waves are rounded up to a whole workgroup
+// (Adam N = 1 K = 7, 1.2 GB: two 398 us, three 347 us; N = 2 K = 6
+// 386 / 361 us).  12 waves against no limit: Adam N = 3 354M x 4 10.54 against
+// 11.39 ms in one placement of the buffers, 9.94 against 9.93 ms in another.
 constexpr int wave_resident(int K, int bytes, bool many = false, bool clip = false, bool outer = false) {
   int waves = 12;
   if (bytes <= 8) waves = 32;
